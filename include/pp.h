@@ -163,13 +163,14 @@ int pp_synth_delta_sum(pp_model* m, float* dst_dev, size_t n, const uint64_t* ke
 int pp_get_counters(pp_model* m, double* flops_fwd, double* flops_bwd, double* adamw_bytes, int64_t* n_trainable);
 
 /* How many contractions (GEMM calls incl. their split-K reduction, attention forward / backward calls) of the most recent
- * pp_local_step ran on the matrix-core (MFMA) kernels and how many on the plain fp32-FMA kernels.  With PP_F32 storage all
- * are plain by design; with PP_BF16 a plain call means a shape or alignment the MFMA kernels do not take (or "force_plain"):
- * the result is still correct, only slow -- tests of the bf16 benchmark shapes assert plain_calls == 0. */
+ * pp_local_step ran on the bf16 matrix-core kernels and how many in fp32 multiplies ("plain": the fp32 MFMA GEMM, which adds in
+ * the order of the vector kernels and returns their bits, or with "force_plain" those).  With PP_F32 storage all are plain by
+ * design; with PP_BF16 a plain call means a shape or alignment the bf16 kernels do not take: the result is still correct,
+ * only slower -- tests of the bf16 benchmark shapes assert plain_calls == 0. */
 int pp_get_launch_counts(pp_model* m, int64_t* matrix_core_calls, int64_t* plain_calls);
 
 /* Options for tests and profiling.  "force_plain": 0 = automatic (MFMA kernels when shapes allow), 1 = force the
- * plain (non-MFMA) kernels.  "dw_tn": 1 (default) = weight-gradient GEMMs read their token-major operands directly
+ * plain (non-MFMA) kernels throughout.  "dw_tn": 1 (default) = weight-gradient GEMMs read their token-major operands directly
  * (LDS transpose reads), 0 = through transposed copies and the NT kernel.  "fuse_rope": 1 (default) = the rotary embedding of
  * q and k is applied in the q|k|v projection's epilogue (one rounding), 0 = as a separate pass over the stored projection.  "time_gemm": 1 = bracket every GEMM launch of later pp_local_step calls with a pair
  * of HIP events on the model's stream (host-side events only; no device memory), 0 = off; setting it resets the totals.

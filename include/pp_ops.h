@@ -19,7 +19,8 @@ extern "C" {
  * out_f32 != 0: C is float (weight gradients); then R must be NULL.
  * splits > 1 (needs out_f32, scratch_dev of M*N*splits floats): K is cut into `splits` equal ranges whose
  * partial products are summed in fixed order into C.
- * path: 0 = automatic (MFMA kernel when dtype is bf16 and K % 64 == 0, lda % 8 == 0, ldb % 8 == 0), 1 = plain kernel. */
+ * path: 0 = automatic (bf16 MFMA kernels when dtype is bf16 and K % 64 == 0, lda % 8 == 0, ldb % 8 == 0, otherwise the fp32-multiply
+ * MFMA kernel, which returns the plain kernel's bits), 1 = plain (vector FMA) kernel. */
 int pp_op_gemm_nt(void* hip_stream, int dtype, const void* A_dev, int lda, const void* B_dev, int ldb, void* C_dev, int ldc,
                   int M, int N, int K, const void* R_dev, int out_f32, int splits, float* scratch_dev, int path);
 

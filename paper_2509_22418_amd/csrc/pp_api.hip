@@ -512,7 +512,8 @@ static void gemm_nt(pp_model* m, const void* A, int lda, const void* B, int ldb,
   if (m->cfg.dtype == PP_BF16 && !m->force_plain &&
       k_gemm_nt_mfma(m->st, A, lda, B, ldb, C, ldc, M, N, K, epi, R, 0, 1, nullptr) == 0) { m->n_mfma++; return; }
   m->n_plain++;
-  k_gemm_nt_plain(m->st, m->cfg.dtype, A, lda, B, ldb, C, ldc, M, N, K, epi, R, 0);
+  if (m->force_plain) k_gemm_nt_plain(m->st, m->cfg.dtype, A, lda, B, ldb, C, ldc, M, N, K, epi, R, 0);
+  else k_gemm_nt_f32(m->st, m->cfg.dtype, A, lda, B, ldb, C, ldc, M, N, K, epi, R, 0, 1, nullptr);
 }
 
 // gate/up projection with the SwiGLU product formed in the GEMM's epilogue; false = not launched (shape or path)
@@ -547,14 +548,18 @@ static bool gemm_swiglu_bwd(pp_model* m, const void* G, const void* Wd_rows, con
 
 // Weight-gradient GEMM: G[M x N] (fp32, ld = N) = At[M x K] * Bt[N x K]^T with K = tokens.  Few output tiles and
 // a long K: the K range is split over `splits` workgroup columns and summed in fixed order.
-static void gemm_dw(pp_model* m, const void* At, const void* Bt, float* G, int M, int N, int K) {
-  if (m->flop_acc) *m->flop_acc += 2.0 * M * N * K;
-  GemmTimer timer(m, 2.0 * M * N * K);
+static int dw_splits(const pp_model* m, int M, int N, int K) {
   const size_t out_bytes = (size_t)M * N * 4;
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
   int splits = 1;
   while (splits < 32 && tiles * splits < 1024 && K % (splits * 2) == 0 && K / (splits * 2) >= 256 &&
          out_bytes * (size_t)(splits * 2) <= m->ws.partial_bytes) splits *= 2;
+  return splits;
+}
+static void gemm_dw(pp_model* m, const void* At, const void* Bt, float* G, int M, int N, int K) {
+  if (m->flop_acc) *m->flop_acc += 2.0 * M * N * K;
+  GemmTimer timer(m, 2.0 * M * N * K);
+  const int splits = dw_splits(m, M, N, K);
   float* partial = (float*)(m->wsp + m->ws.partial);
   if (m->cfg.dtype == PP_BF16 && !m->force_plain &&
       k_gemm_nt_mfma(m->st, At, K, Bt, K, G, N, M, N, K, EPI_STORE, nullptr, 1, splits, partial) == 0) {
@@ -563,6 +568,11 @@ static void gemm_dw(pp_model* m, const void* At, const void* Bt, float* G, int M
     return;
   }
   m->n_plain++;
+  if (!m->force_plain) {
+    k_gemm_nt_f32(m->st, m->cfg.dtype, At, K, Bt, K, G, N, M, N, K, EPI_STORE, nullptr, 1, splits, partial);
+    if (splits > 1) k_splitk_reduce(m->st, partial, G, N, M, N, splits);
+    return;
+  }
   if (splits == 1) { k_gemm_nt_plain(m->st, m->cfg.dtype, At, K, Bt, K, G, N, M, N, K, EPI_STORE, nullptr, 1); return; }
   k_gemm_nt_plain_splitk(m->st, m->cfg.dtype, At, K, Bt, K, partial, M, N, K, splits);
   k_splitk_reduce(m->st, partial, G, N, M, N, splits);
@@ -589,6 +599,18 @@ static void gemm_dw_tn(pp_model* m, const void* A, int lda, int m_blk, long a_bl
       if (splits > 1) k_splitk_reduce(m->st, partial, G, N, M, N, splits);
       if (m->flop_acc) *m->flop_acc += 2.0 * M * N * K;
       m->n_mfma++;
+      return;
+    }
+    timer.cancel();
+  }
+  if (m->cfg.dtype == PP_F32 && !m->force_plain) {          // fp32: token-major operands too; same K ranges and order of sums as below
+    const int splits = dw_splits(m, M, N, K);
+    float* partial = (float*)(m->wsp + m->ws.partial);
+    GemmTimer timer(m, 2.0 * M * N * K);
+    if (k_gemm_tn_f32(m->st, (const float*)A, lda, m_blk, a_blk_stride, (const float*)B, ldb, G, N, M, N, K, splits, partial) == 0) {
+      if (splits > 1) k_splitk_reduce(m->st, partial, G, N, M, N, splits);
+      if (m->flop_acc) *m->flop_acc += 2.0 * M * N * K;
+      m->n_plain++;
       return;
     }
     timer.cancel();
@@ -907,6 +929,7 @@ extern "C" int pp_op_gemm_nt(void* hip_stream, int dtype, const void* A, int lda
   bool done = false;
   if (path == 0 && dtype == PP_BF16)
     done = k_gemm_nt_mfma(st, A, lda, B, ldb, C, ldc, M, N, K, epi, R, out_f32, splits, scratch) == 0;
+  if (!done && path == 0) { k_gemm_nt_f32(st, dtype, A, lda, B, ldb, C, ldc, M, N, K, epi, R, f32out ? 1 : 0, splits, scratch); done = true; }
   if (!done) {
     if (splits > 1) k_gemm_nt_plain_splitk(st, dtype, A, lda, B, ldb, scratch, M, N, K, splits);
     else k_gemm_nt_plain(st, dtype, A, lda, B, ldb, C, ldc, M, N, K, epi, R, f32out ? 1 : 0);
@@ -968,7 +991,10 @@ extern "C" int pp_op_gemm_nt_splitk_static(void* hip_stream, int dtype, const vo
   if (int rc = static_scratch(&part)) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   // every element [z][row < M][col < N] of the partials is written by the GEMM before the reduction reads it: nothing to clear
-  if (!(path == 0 && dtype == PP_BF16 && k_gemm_nt_mfma(st, A, lda, B, ldb, C, ldc, M, N, K, EPI_STORE, nullptr, 1, splits, part) == 0))
+  if (path == 0) {
+    if (!(dtype == PP_BF16 && k_gemm_nt_mfma(st, A, lda, B, ldb, C, ldc, M, N, K, EPI_STORE, nullptr, 1, splits, part) == 0))
+      k_gemm_nt_f32(st, dtype, A, lda, B, ldb, C, ldc, M, N, K, EPI_STORE, nullptr, 1, splits, part);
+  } else
     k_gemm_nt_plain_splitk(st, dtype, A, lda, B, ldb, part, M, N, K, splits);
   k_splitk_reduce(st, part, C, ldc, M, N, splits);
   hipError_t e = hipGetLastError();

@@ -53,6 +53,15 @@ void k_gemm_nt_plain_splitk(hipStream_t st, int dtype, const void* A, int lda, c
                             int M, int N, int K, int splits);
 void k_splitk_reduce(hipStream_t st, const float* partial, float* C, int ldc, int M, int N, int splits);
 
+// fp32-multiply MFMA GEMMs, any shape and alignment, fp32 or bf16 storage (pp_gemm_f32.hip).  K % splits == 0; splits > 1:
+// `partial` receives [splits][M][N] floats and C is not written (k_splitk_reduce sums them).
+void k_gemm_nt_f32(hipStream_t st, int dtype, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, int epi, const void* R,
+                   int out_f32, int splits, float* partial);
+// C[M x N] fp32 = A^T B, A's columns in blocks as in k_gemm_tn_mfma; returns 1 (nothing launched) if M > m_blk and a group of four
+// columns could straddle two blocks
+int k_gemm_tn_f32(hipStream_t st, const float* A, int lda, int m_blk, long a_blk_stride, const float* B, int ldb, float* C, int ldc, int M, int N, int K,
+                  int splits, float* partial);
+
 void k_attn_fwd_plain(hipStream_t st, int dtype, const void* qkv, void* o, float* lse, int B, int S, int h, int dh);
 void k_attn_D(hipStream_t st, int dtype, const void* o, const void* dO, float* Dbuf, int B, int S, int h, int dh);
 void k_attn_bwd_plain(hipStream_t st, int dtype, const void* qkv, const void* o, const float* lse, const void* dO, void* dqkv,
