@@ -586,17 +586,19 @@ static void gemm_dw_tn(pp_model* m, const void* A, int lda, int m_blk, long a_bl
   const size_t es = esize(m->cfg);
   // (measured at K = 16384: up to 256 tiles of 128 x 128 -- the row-block slices, which need split-K anyway, and d x d --
   // the transpose-read kernel beats transposing both operands and running the 256 x 256-tile NT kernel; above that the
-  // NT kernel's higher rate outweighs the two extra passes)
+  // NT kernel's higher rate outweighs the two extra passes.  A token count that is not a multiple of 64 always comes here: the
+  // transposed copies would have rows the NT kernel does not take.)
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if (m->cfg.dtype == PP_BF16 && !m->force_plain && m->dw_tn && tiles <= 256) {
+  if (m->cfg.dtype == PP_BF16 && !m->force_plain && m->dw_tn && (tiles <= 256 || K % 64)) {
     const size_t out_bytes = (size_t)M * N * 4;
     int splits = 1;
-    while (splits < 32 && tiles * splits < 512 && K % (splits * 2 * 64) == 0 && K / (splits * 2) >= 256 &&
+    while (splits < 32 && tiles * splits < 512 && (K % (splits * 2 * 64) == 0 || K % 64) && K / (splits * 2) >= 256 &&
            out_bytes * (size_t)(splits * 2) <= m->ws.partial_bytes) splits *= 2;
+    const int kchunk = ((K + splits - 1) / splits + 63) / 64 * 64, ranges = (K + kchunk - 1) / kchunk;
     float* partial = (float*)(m->wsp + m->ws.partial);
     GemmTimer timer(m, 2.0 * M * N * K);
-    if (k_gemm_tn_mfma(m->st, A, lda, m_blk, a_blk_stride, B, ldb, G, N, M, N, K, splits, partial) == 0) {
-      if (splits > 1) k_splitk_reduce(m->st, partial, G, N, M, N, splits);
+    if (k_gemm_tn_mfma(m->st, A, lda, m_blk, a_blk_stride, B, ldb, G, N, M, N, K, kchunk, partial) == 0) {
+      if (ranges > 1) k_splitk_reduce(m->st, partial, G, N, M, N, ranges);
       if (m->flop_acc) *m->flop_acc += 2.0 * M * N * K;
       m->n_mfma++;
       return;
@@ -947,7 +949,9 @@ extern "C" int pp_op_gemm_tn(void* hip_stream, const void* A, int lda, int m_blk
   if ((int64_t)((M - 1) / m_blk) * a_blk_stride + std::min(M, m_blk) > lda) return fail(PP_EINVAL, "pp_op_gemm_tn: column blocks of A exceed lda");
   if (splits < 1 || (splits > 1 && !scratch)) return fail(PP_EINVAL, "pp_op_gemm_tn: split-K needs a scratch buffer");
   hipStream_t st = (hipStream_t)hip_stream;
-  if (k_gemm_tn_mfma(st, A, lda, m_blk, (long)a_blk_stride, B, ldb, C, ldc, M, N, K, splits, scratch) != 0)
+  // ranges of whole K steps, and column blocks of whole 128-column tiles (the step's own dispatch takes more)
+  const bool taken = (long)splits * 64 <= K && K % ((long)splits * 64) == 0 && !(M > m_blk && m_blk % 128);
+  if (!taken || k_gemm_tn_mfma(st, A, lda, m_blk, (long)a_blk_stride, B, ldb, C, ldc, M, N, K, K / splits, scratch) != 0)
     return fail(PP_EINVAL, "pp_op_gemm_tn: shape or alignment not taken by the MFMA kernel (see pp_ops.h)");
   if (splits > 1) k_splitk_reduce(st, scratch, C, ldc, M, N, splits);
   hipError_t e = hipGetLastError();

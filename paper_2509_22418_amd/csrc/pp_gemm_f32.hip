@@ -228,12 +228,19 @@ static void launch_f32(hipStream_t st, const void* A, const void* B, void* C, co
   else launch_f32<T, TO, TN, false>(st, A, B, C, R, g, splits);
 }
 
+// Offsets within a tile's 64 rows (NT: plus all of K) are 32-bit: rows of 8 M elements and more stay on the vector kernel.
+static bool offsets_fit(int lda, int ldb, int K) { return (64ull * (size_t)(lda > ldb ? lda : ldb) + (size_t)K) * 4 < 0x7f000000ull; }
 // rows of groups of four elements that can be read at once
 static bool vec4_ok(int dtype, const void* p, int ld) { return ld % 4 == 0 && ((uintptr_t)p & (dtype == 0 ? 15 : 7)) == 0; }
 
 void k_gemm_nt_f32(hipStream_t st, int dtype, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, int epi, const void* R,
                    int out_f32, int splits, float* partial) {
   if (M == 0 || N == 0) return;
+  if (!offsets_fit(lda, ldb, K)) {
+    if (splits > 1) k_gemm_nt_plain_splitk(st, dtype, A, lda, B, ldb, partial, M, N, K, splits);
+    else k_gemm_nt_plain(st, dtype, A, lda, B, ldb, C, ldc, M, N, K, epi, R, out_f32);
+    return;
+  }
   const F32GemmArgs g{lda, ldb, splits > 1 ? N : ldc, M, N, K, K / splits, M, 0, epi};
   const bool vec = vec4_ok(dtype, A, lda) && vec4_ok(dtype, B, ldb) && g.kchunk % 4 == 0;
   void* out = splits > 1 ? (void*)partial : C;
@@ -242,10 +249,10 @@ void k_gemm_nt_f32(hipStream_t st, int dtype, const void* A, int lda, const void
   else launch_f32<bf16_t, bf16_t, false>(st, A, B, out, R, g, splits, vec);
 }
 
-// returns 1 (nothing launched) if a group of four columns of A could straddle two column blocks
+// returns 1 (nothing launched) if a group of four columns of A could straddle two column blocks, or rows are too long for the offsets
 int k_gemm_tn_f32(hipStream_t st, const float* A, int lda, int m_blk, long a_blk_stride, const float* B, int ldb, float* C, int ldc, int M, int N, int K,
                   int splits, float* partial) {
-  if (M > m_blk && (m_blk % 4 || a_blk_stride % 4)) return 1;
+  if ((M > m_blk && (m_blk % 4 || a_blk_stride % 4)) || !offsets_fit(lda, ldb, 0)) return 1;
   if (M == 0 || N == 0) return 0;
   const F32GemmArgs g{lda, ldb, splits > 1 ? N : ldc, M, N, K, K / splits, m_blk, a_blk_stride, EPI_STORE};
   const bool vec = vec4_ok(0, A, lda) && vec4_ok(0, B, ldb) && M % 4 == 0 && N % 4 == 0;

@@ -41,10 +41,14 @@ constexpr int TN_LDS_BYTES = 2 * TN_STAGE_BYTES;
 
 // A's columns may come in blocks: column m of the product is column (m / m_blk) * a_blk_stride + m % m_blk of A
 // (gate and up gradients of a hidden-unit slice sit d_ff columns apart; the Q, K, V parts of a head range d_model apart).
-// A tile never straddles two blocks (the launcher requires m_blk % 128 == 0 whenever M > m_blk).
+// Blocks are multiples of 8 columns, so a 16-byte chunk never straddles two of them; every lane finds its own chunk's block once.
+// K need not be a multiple of 64: in the last step the rows past the end are loaded from the last row (in bounds) and then
+// overwritten with zeros in both panels, so neither their values nor infinities among them reach a product.  (A token count that
+// is not a multiple of 64 used to send every weight gradient through element-wise transposes and fp32 multiplies: 4 layers of
+// 768 x 3072 on 3055 tokens spent 12.8 ms there.)
 __global__ __launch_bounds__(256, 2) void gemm_tn_mfma_kernel(const bf16_t* __restrict__ A, int lda, int m_blk, long a_blk_stride,
                                                                const bf16_t* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-                                                               int M, int N, int Ksplit, int tiles_m, int tiles_n) {
+                                                               int M, int N, int K, int Ksplit, int tiles_m, int tiles_n) {
   extern __shared__ __align__(16) unsigned char tn_lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -65,7 +69,8 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_mfma_kernel(const bf16_t* __re
   const int tm = first_m + in_group % gsz, tn = in_group / gsz;
   const int m0 = tm * TN_BM, n0 = tn * TN_BN;
   const size_t kbase = (size_t)z * Ksplit;
-  const int ns = Ksplit / TN_BK;
+  const int kz = min(Ksplit, K - (int)kbase);          // rows of this range (>= 1)
+  const int ns = (kz + TN_BK - 1) / TN_BK, last = kz - (ns - 1) * TN_BK;          // rows of the last step
 
   // ---- direct-to-LDS fill: wave w moves wave-loads 4w .. 4w+3 of each operand tile; wave-load q = rows 4q .. 4q+3,
   // lane l -> row 4q + l/16, chunk position l%16, which receives source chunk (l%16) ^ ((row & 3) << 2).
@@ -73,17 +78,27 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_mfma_kernel(const bf16_t* __re
   const int fchunk = (lane & 15) ^ (frow << 2);                        // source chunk of this lane
   const int a_valid = min(M, m0 + TN_BM) - m0, b_valid = min(N, n0 + TN_BN) - n0;          // columns of the tile that exist (multiples of 8)
   const int a_col = min(fchunk * 8, a_valid - 8), b_col = min(fchunk * 8, b_valid - 8);    // clamped: padded columns repeat the last chunk
-  const long a_col0 = (long)(m0 / m_blk) * a_blk_stride + (m0 % m_blk);
-  const bf16_t* gA = A + (kbase + (size_t)(wave * 16 + frow)) * lda + a_col0 + a_col;
+  const int am = m0 + a_col;
+  const bf16_t* gA = A + (kbase + (size_t)(wave * 16 + frow)) * lda + (long)(am / m_blk) * a_blk_stride + (am % m_blk);
   const bf16_t* gB = B + (kbase + (size_t)(wave * 16 + frow)) * ldb + n0 + b_col;
   auto issue = [&](int s, int stage) {          // K-step s into LDS stage `stage`: 8 loads per wave
     unsigned char* dst = tn_lds + stage * TN_STAGE_BYTES + wave * 4 * 1024;
-    const size_t ka = (size_t)s * TN_BK * lda, kb = (size_t)s * TN_BK * ldb;
+    if (s < ns - 1 || last == TN_BK) {
+      const size_t ka = (size_t)s * TN_BK * lda, kb = (size_t)s * TN_BK * ldb;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) __builtin_amdgcn_global_load_lds(PP_TN_GPTR(gA + ka + (size_t)(4 * i) * lda), PP_TN_LPTR(dst + i * 1024), 16, 0, 0);
+      for (int i = 0; i < 4; ++i) __builtin_amdgcn_global_load_lds(PP_TN_GPTR(gA + ka + (size_t)(4 * i) * lda), PP_TN_LPTR(dst + i * 1024), 16, 0, 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds(PP_TN_GPTR(gB + kb + (size_t)(4 * i) * ldb), PP_TN_LPTR(dst + TN_OPERAND_BYTES + i * 1024), 16, 0, 0);
+      for (int i = 0; i < 4; ++i)
+        __builtin_amdgcn_global_load_lds(PP_TN_GPTR(gB + kb + (size_t)(4 * i) * ldb), PP_TN_LPTR(dst + TN_OPERAND_BYTES + i * 1024), 16, 0, 0);
+    } else {          // a short last step: rows past the end repeat the last one
+      const int r0 = wave * 16 + frow;          // row of gA / gB within a step
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const long dr = (long)s * TN_BK + min(r0 + 4 * i, last - 1) - r0;
+        __builtin_amdgcn_global_load_lds(PP_TN_GPTR(gA + dr * lda), PP_TN_LPTR(dst + i * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(PP_TN_GPTR(gB + dr * ldb), PP_TN_LPTR(dst + TN_OPERAND_BYTES + i * 1024), 16, 0, 0);
+      }
+    }
   };
 
   // ---- fragment addresses.  Lane l: j = l % 16 (position in its group of 16), grp = l / 16: column half grp & 1 of a
@@ -131,6 +146,15 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_mfma_kernel(const bf16_t* __re
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     if (s + 1 < ns) issue(s + 1, (s + 1) & 1);
+    else if (last < TN_BK) {          // rows past the end of K: zeros in both panels (nothing is in flight any more)
+      unsigned char* z0 = tn_lds + (s & 1) * TN_STAGE_BYTES + last * 256;
+      const int n16 = (TN_BK - last) * 16;
+      for (int i = tid; i < 2 * n16; i += 256)
+        *reinterpret_cast<uint4*>(z0 + (i < n16 ? i : i - n16) * 16 + (i < n16 ? 0 : TN_OPERAND_BYTES)) = make_uint4(0, 0, 0, 0);
+      __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0)
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
     const unsigned char* stage = tn_lds + (s & 1) * TN_STAGE_BYTES;
     read_frags(0, stage, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -166,23 +190,23 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_mfma_kernel(const bf16_t* __re
     }
 }
 
-// C[M x N] fp32 (ldc) = A^T B over K rows; splits > 1: `partial` receives [splits][M][N] (C is not written; the caller sums
-// the partials in fixed order).  Returns 0 if launched, 1 if the shapes are not taken (nothing launched).
+// C[M x N] fp32 (ldc) = A^T B over K rows in ranges of `kchunk` (a multiple of 64; the last may be shorter); more than one range:
+// `partial` receives [ranges][M][N] (C is not written; the caller sums the partials in fixed order).  Returns 0 if launched, 1 if
+// the shapes are not taken (nothing launched).
 int k_gemm_tn_mfma(hipStream_t st, const void* A, int lda, int m_blk, long a_blk_stride, const void* B, int ldb, float* C, int ldc,
-                   int M, int N, int K, int splits, float* partial) {
-  if (M < 8 || N < 8 || (M & 7) || (N & 7) || (lda & 7) || (ldb & 7) || splits < 1 || K < 1) return 1;
-  if (K % (splits * 64)) return 1;
+                   int M, int N, int K, int kchunk, float* partial) {
+  if (M < 8 || N < 8 || (M & 7) || (N & 7) || (lda & 7) || (ldb & 7) || K < 1 || kchunk < 64 || (kchunk & 63)) return 1;
   if (m_blk < 1 || (m_blk & 7) || (a_blk_stride & 7)) return 1;
-  if (M > m_blk && (m_blk % TN_BM)) return 1;          // a tile must not straddle two column blocks of A
   if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C | (uintptr_t)partial) & 15) return 1;
+  const int splits = (int)(((long)K + kchunk - 1) / kchunk);
   if (splits > 1 && !partial) return 1;
   static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_mfma_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, TN_LDS_BYTES) == hipSuccess;
   if (!ok) return 1;
   const int tiles_m = (M + TN_BM - 1) / TN_BM, tiles_n = (N + TN_BN - 1) / TN_BN;
   dim3 grid(tiles_m * tiles_n, splits);
   float* out = splits > 1 ? partial : C;
-  gemm_tn_mfma_kernel<<<grid, 256, TN_LDS_BYTES, st>>>((const bf16_t*)A, lda, m_blk, a_blk_stride, (const bf16_t*)B, ldb, out, splits > 1 ? N : ldc, M, N,
-                                                       K / splits, tiles_m, tiles_n);
+  gemm_tn_mfma_kernel<<<grid, 256, TN_LDS_BYTES, st>>>((const bf16_t*)A, lda, m_blk, a_blk_stride, (const bf16_t*)B, ldb, out, splits > 1 ? N : ldc, M, N, K,
+                                                       kchunk, tiles_m, tiles_n);
   return 0;
 }
 

@@ -91,10 +91,11 @@ int k_gemm_qkv_rope_mfma(hipStream_t st, const void* X, int ldx, const void* Wqk
 int k_gemm_nt_mfma(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K,
                    int epi, const void* R, int out_f32, int splits, float* partial);
 // Weight-gradient form: C[M x N] fp32 (ldc) = A^T B with A [K x M] (lda), B [K x N] (ldb) row-major bf16 -- no transposed
-// copies.  Column m of the product is column (m / m_blk) * a_blk_stride + m % m_blk of A.  splits > 1: `partial` receives
-// [splits][M][N] and C is not written.  Returns 0 if launched, 1 if the shape is not taken.
+// copies.  Column m of the product is column (m / m_blk) * a_blk_stride + m % m_blk of A.  K is cut into ranges of `kchunk` rows (a
+// multiple of 64); with more than one, `partial` receives [ranges][M][N] and C is not written.  Returns 0 if launched, 1 if the
+// shape is not taken.
 int k_gemm_tn_mfma(hipStream_t st, const void* A, int lda, int m_blk, long a_blk_stride, const void* B, int ldb, float* C, int ldc,
-                   int M, int N, int K, int splits, float* partial);
+                   int M, int N, int K, int kchunk, float* partial);
 // 128 x 128-tile variant for shapes with too few 256 x 256 tiles to fill the chip (bf16 out, EPI_STORE / EPI_ADD_RES)
 int k_gemm_nt128_mfma(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, int epi, const void* R);
 void gemm_set_small_tiles(int v);      // 1 (default): k_gemm_nt_mfma hands GEMMs with at most 128 tiles of 256 x 256 (half a tile per compute unit) to the 128 x 128 kernel
