@@ -14,15 +14,15 @@
 // v_mfma_f32_32x32x16_bf16, 64 accumulator registers); K advances in steps of 64 rows; two LDS stages of 16 KB per
 // operand (64 KB per workgroup, two workgroups per compute unit), the next step's tiles in flight while the current one
 // is multiplied, one barrier per step.  (A ring of four 32-row stages with three steps in flight was measured slower on
-// every shape: the cost per step is the barrier and the first fragment reads behind it, not the loads.)  Within a step the
-// fragment registers are double-buffered: the transpose reads of the next 16-row slice are slotted between the MFMAs of
-// the current one.  Tiles are filled by direct-to-LDS loads (one wave
-// load = 4 rows); the 16-byte chunk c of row r is stored at chunk c ^ ((r & 3) << 2), applied on the source side, so
+// every shape: the cost per step is the barrier and the first fragment reads behind it, not the loads.)  Tiles are filled
+// by direct-to-LDS loads (one wave load = 4 rows); the 16-byte chunk c of row r is stored at chunk c ^ ((r & 3) << 2), applied on the source side, so
 // that the 4 rows x 2 x 32 bytes touched by one phase of a transpose read fall into 8 different 32-byte bank groups.
 // Few output tiles and a long K: the K range is split over blockIdx.y; partial products are summed in fixed order by
 // the caller (k_splitk_reduce), so the result is reproducible run to run.
 #include "pp_kernels.h"
 #include "pp_dev.h"
+
+#include <type_traits>
 
 namespace pp {
 
@@ -48,7 +48,7 @@ constexpr int TN_LDS_BYTES = 2 * TN_STAGE_BYTES;
 // 768 x 3072 on 3055 tokens spent 12.8 ms there.)
 __global__ __launch_bounds__(256, 2) void gemm_tn_mfma_kernel(const bf16_t* __restrict__ A, int lda, int m_blk, long a_blk_stride,
                                                                const bf16_t* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-                                                               int M, int N, int K, int Ksplit, int tiles_m, int tiles_n) {
+                                                               int M, int N, int K, int Ksplit, int sub_steps, int tiles_m, int tiles_n) {
   extern __shared__ __align__(16) unsigned char tn_lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -112,33 +112,49 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_mfma_kernel(const bf16_t* __re
   };
   const int offA0 = frag_off(wm, 0), offA1 = frag_off(wm, 1);
   const int offB0 = TN_OPERAND_BYTES + frag_off(wn, 0), offB1 = TN_OPERAND_BYTES + frag_off(wn, 1);
-  auto frag = [&](const unsigned char* stage, int off, int kk) -> bf16x8 {          // 8 consecutive k (rows 16 kk + 8 (grp >> 1) ..) of one column
-    const unsigned char* p = stage + off + kk * 16 * 256;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)PP_TN_LPTR(const_cast<unsigned char*>(p)));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)PP_TN_LPTR(const_cast<unsigned char*>(p + 4 * 256)));
-    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
+  // One K16 slice's four fragments: 8 consecutive k (rows 16 kk + 8 (grp >> 1) ..) of one column each, two transpose reads per
+  // fragment.  In assembly because of the builtin's waits: while direct-to-LDS loads are pending the compiler waits for all of
+  // them (vmcnt(0)) in front of every transpose read, i.e. for the NEXT step's tiles right after they were requested; nothing of
+  // a step's load latency was hidden inside a workgroup.  The reads are waited for inside the block, so its outputs are ready.
+  // (K = 16384, before / after: 2048 x 2048 unsplit, one workgroup per unit, 252 / 201 us; 6144 x 2048 563 / 476; 32000 x 768 over
+  // 3072 rows 186 / 172; shapes with two workgroups per unit that hid each other's loads stay as they were.  Turning the tiles in
+  // registers on their way into LDS instead, so that plain 16-byte reads serve as fragments, was slower: 77 against 61 us at
+  // 512 x 2048 in 16 ranges.)
+  bf16x8 fa[2], fb[2];
+  auto read_frags = [&](uint32_t st, auto KK) {          // st = byte offset of the stage in LDS
+    constexpr int k0 = decltype(KK)::value * 16 * 256;
+    s16x4 r[8];
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8 offset:%12\n\tds_read_b64_tr_b16 %1, %8 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %2, %9 offset:%12\n\tds_read_b64_tr_b16 %3, %9 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %4, %10 offset:%12\n\tds_read_b64_tr_b16 %5, %10 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %6, %11 offset:%12\n\tds_read_b64_tr_b16 %7, %11 offset:%13\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+        : "v"(st + offA0), "v"(st + offA1), "v"(st + offB0), "v"(st + offB1), "n"(k0), "n"(k0 + 4 * 256)
+        : "memory");
+    auto join = [](s16x4 lo, s16x4 hi) { return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)); };
+    fa[0] = join(r[0], r[1]); fa[1] = join(r[2], r[3]);
+    fb[0] = join(r[4], r[5]); fb[1] = join(r[6], r[7]);
   };
 
-  f32x16 acc[2][2];
+  // acc: running sum of up to sub_steps steps; tot: sum of the finished ones, so that a range that covers several of the caller's
+  // ranges keeps their shorter fp32 chains
+  f32x16 acc[2][2], tot[2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+      for (int r = 0; r < 16; ++r) { acc[a][b][r] = 0.f; tot[a][b][r] = 0.f; }
 
-  bf16x8 fa[2][2], fb[2][2];
-  auto read_frags = [&](int buf, const unsigned char* stage, int kk) {
-    fa[buf][0] = frag(stage, offA0, kk); fa[buf][1] = frag(stage, offA1, kk);
-    fb[buf][0] = frag(stage, offB0, kk); fb[buf][1] = frag(stage, offB1, kk);
+  auto mm = [&]() {
+    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0], fb[0], acc[0][0], 0, 0, 0);
+    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0], fb[1], acc[0][1], 0, 0, 0);
+    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1], fb[0], acc[1][0], 0, 0, 0);
+    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1], fb[1], acc[1][1], 0, 0, 0);
   };
-  auto mm = [&](int buf) {
-    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][0], fb[buf][0], acc[0][0], 0, 0, 0);
-    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][0], fb[buf][1], acc[0][1], 0, 0, 0);
-    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][1], fb[buf][0], acc[1][0], 0, 0, 0);
-    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][1], fb[buf][1], acc[1][1], 0, 0, 0);
-  };
+  const uint32_t lds0 = (uint32_t)(uintptr_t)PP_TN_LPTR(tn_lds);
   issue(0, 0);
   for (int s = 0; s < ns; ++s) {
     // this wave's loads of step s have landed; after the barrier everybody's have, and nobody reads the other stage any more
@@ -155,21 +171,19 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_mfma_kernel(const bf16_t* __re
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
     }
-    const unsigned char* stage = tn_lds + (s & 1) * TN_STAGE_BYTES;
-    read_frags(0, stage, 0);
+    const uint32_t stage = lds0 + (s & 1) * TN_STAGE_BYTES;
     __builtin_amdgcn_sched_barrier(0);
+    read_frags(stage, std::integral_constant<int, 0>{}); mm();
+    read_frags(stage, std::integral_constant<int, 1>{}); mm();
+    read_frags(stage, std::integral_constant<int, 2>{}); mm();
+    read_frags(stage, std::integral_constant<int, 3>{}); mm();
+    if ((s + 1) % sub_steps == 0 || s + 1 == ns) {
 #pragma unroll
-    for (int kk = 0; kk < TN_BK / 16; ++kk) {
-      if (kk + 1 < TN_BK / 16) read_frags((kk + 1) & 1, stage, kk + 1);
-      mm(kk & 1);
-      if (kk + 1 < TN_BK / 16) {          // one MFMA, then two of the next slice's eight transpose reads, four times
+      for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) { tot[a][b][r] += acc[a][b][r]; acc[a][b][r] = 0.f; }
     }
   }
 
@@ -185,17 +199,18 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_mfma_kernel(const bf16_t* __re
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = m0 + wm * 64 + a * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-        if (row < M && col < N) Cz[(size_t)row * ldc + col] = acc[a][b][r];
+        if (row < M && col < N) Cz[(size_t)row * ldc + col] = tot[a][b][r];
       }
     }
 }
 
-// C[M x N] fp32 (ldc) = A^T B over K rows in ranges of `kchunk` (a multiple of 64; the last may be shorter); more than one range:
+// C[M x N] fp32 (ldc) = A^T B over K rows in ranges of `kchunk` (a multiple of 64; the last may be shorter), each summed in pieces of
+// `sub` rows (a multiple of 64, >= kchunk: one piece) that are added in order; more than one range:
 // `partial` receives [ranges][M][N] (C is not written; the caller sums the partials in fixed order).  Returns 0 if launched, 1 if
 // the shapes are not taken (nothing launched).
 int k_gemm_tn_mfma(hipStream_t st, const void* A, int lda, int m_blk, long a_blk_stride, const void* B, int ldb, float* C, int ldc,
-                   int M, int N, int K, int kchunk, float* partial) {
-  if (M < 8 || N < 8 || (M & 7) || (N & 7) || (lda & 7) || (ldb & 7) || K < 1 || kchunk < 64 || (kchunk & 63)) return 1;
+                   int M, int N, int K, int kchunk, float* partial, int sub) {
+  if (M < 8 || N < 8 || (M & 7) || (N & 7) || (lda & 7) || (ldb & 7) || K < 1 || kchunk < 64 || (kchunk & 63) || sub < 64 || (sub & 63)) return 1;
   if (m_blk < 1 || (m_blk & 7) || (a_blk_stride & 7)) return 1;
   if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C | (uintptr_t)partial) & 15) return 1;
   const int splits = (int)(((long)K + kchunk - 1) / kchunk);
@@ -206,7 +221,7 @@ int k_gemm_tn_mfma(hipStream_t st, const void* A, int lda, int m_blk, long a_blk
   dim3 grid(tiles_m * tiles_n, splits);
   float* out = splits > 1 ? partial : C;
   gemm_tn_mfma_kernel<<<grid, 256, TN_LDS_BYTES, st>>>((const bf16_t*)A, lda, m_blk, a_blk_stride, (const bf16_t*)B, ldb, out, splits > 1 ? N : ldc, M, N, K,
-                                                       kchunk, tiles_m, tiles_n);
+                                                       kchunk, sub / 64, tiles_m, tiles_n);
   return 0;
 }
 

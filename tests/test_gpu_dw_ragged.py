@@ -2,6 +2,7 @@
 whole tiles: a bf16 step against the same step on the plain kernels."""
 import numpy as np
 import pytest
+import torch
 
 import pp_inputs as gen
 import paper_2509_22418_amd as pp
@@ -40,3 +41,20 @@ def test_ragged_token_counts_match_the_plain_kernels(B, S, mname):
     assert np.all(np.isfinite(g[0]))
     assert cosine(g[0], g[1]) >= 0.9995
     assert np.linalg.norm(g[0] - g[1]) <= 0.02 * np.linalg.norm(g[1])
+
+
+@pytest.mark.parametrize("M,N,splits", [(1024, 2048, 8), (1024, 2048, 4), (1160, 2056, 16), (1160, 2056, 6)])
+def test_more_ranges_than_fill_the_gpu_are_joined(M, N, splits):
+    """128 and 170 tiles: four and eight (but not six) ranges are run as fewer.  fp32 sums of at most K products and `splits` partial
+    sums: (K + splits) half-ulp roundings of sum |a b| bound the error, and no partial is left out or added twice."""
+    K = 64 * splits * 2
+    g = torch.Generator(device="cuda").manual_seed(9)
+    A = torch.randn(K, M, device="cuda", generator=g).bfloat16()
+    B = torch.randn(K, N, device="cuda", generator=g).bfloat16()
+    C = torch.full((M, N), float("nan"), device="cuda")
+    scratch = torch.full((M * N * splits,), float("nan"), device="cuda")
+    pp.pp_op_gemm_tn(torch.cuda.current_stream().cuda_stream, A.data_ptr(), M, M, 0, B.data_ptr(), N, C.data_ptr(), N, M, N, K, splits, scratch.data_ptr())
+    torch.cuda.synchronize()
+    ref = A.double().T.contiguous() @ B.double()
+    bound = A.double().abs().T.contiguous() @ B.double().abs()
+    assert bool(((C.double() - ref).abs() <= (K + splits) * 2.0 ** -24 * bound).all())
