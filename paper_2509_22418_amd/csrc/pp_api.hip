@@ -630,7 +630,7 @@ static void attn_fwd(pp_model* m, const void* qkv, void* o, float* lse, int B, i
   if (m->flop_acc) *m->flop_acc += 4.0 * ((double)B * S * (S + 1) / 2) * m->cfg.d_model;
   if (m->cfg.dtype == PP_BF16 && !m->force_plain && k_attn_fwd_mfma(m->st, qkv, o, lse, B, S, h, dh) == 0) { m->n_mfma++; return; }
   m->n_plain++;
-  k_attn_fwd_plain(m->st, m->cfg.dtype, qkv, o, lse, B, S, h, dh);
+  if (m->force_plain || k_attn_fwd_f32(m->st, m->cfg.dtype, qkv, o, lse, B, S, h, dh) != 0) k_attn_fwd_plain(m->st, m->cfg.dtype, qkv, o, lse, B, S, h, dh);
 }
 // attention backward followed by the rotary embedding's backward on dq, dk (fused into the MFMA kernels' epilogues)
 static void attn_bwd(pp_model* m, const void* qkv, const void* o, const float* lse, const void* dO, void* dqkv, float* Dbuf, int B, int S,
@@ -640,7 +640,8 @@ static void attn_bwd(pp_model* m, const void* qkv, const void* o, const float* l
   if (m->cfg.dtype == PP_BF16 && !m->force_plain &&
       k_attn_bwd_mfma(m->st, qkv, o, lse, dO, dqkv, Dbuf, B, S, h, dh, cosb, sinb) == 0) { m->n_mfma++; return; }
   m->n_plain++;
-  k_attn_bwd_plain(m->st, m->cfg.dtype, qkv, o, lse, dO, dqkv, Dbuf, B, S, h, dh);
+  if (m->force_plain || k_attn_bwd_f32(m->st, m->cfg.dtype, qkv, o, lse, dO, dqkv, Dbuf, B, S, h, dh) != 0)
+    k_attn_bwd_plain(m->st, m->cfg.dtype, qkv, o, lse, dO, dqkv, Dbuf, B, S, h, dh);
   k_rope(m->st, m->cfg.dtype, dqkv, cosb, sinb, B, S, h, dh, 1);
 }
 
@@ -1021,7 +1022,8 @@ extern "C" int pp_op_attention_fwd(void* hip_stream, int dtype, const void* qkv,
   if (!qkv || !o || !lse) return fail(PP_EINVAL, "pp_op_attention_fwd: NULL pointer");
   if (int rc = check_attn(dtype, B, S, h, dh)) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
-  if (!(path == 0 && dtype == PP_BF16 && k_attn_fwd_mfma(st, qkv, o, lse, B, S, h, dh) == 0)) k_attn_fwd_plain(st, dtype, qkv, o, lse, B, S, h, dh);
+  if (!(path == 0 && ((dtype == PP_BF16 && k_attn_fwd_mfma(st, qkv, o, lse, B, S, h, dh) == 0) || k_attn_fwd_f32(st, dtype, qkv, o, lse, B, S, h, dh) == 0)))
+    k_attn_fwd_plain(st, dtype, qkv, o, lse, B, S, h, dh);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PP_EHIP, std::string("pp_op_attention_fwd: ") + hipGetErrorString(e));
   return PP_OK;
@@ -1031,7 +1033,8 @@ extern "C" int pp_op_attention_bwd(void* hip_stream, int dtype, const void* qkv,
   if (!qkv || !o || !lse || !dO || !dqkv || !Dbuf) return fail(PP_EINVAL, "pp_op_attention_bwd: NULL pointer");
   if (int rc = check_attn(dtype, B, S, h, dh)) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
-  if (!(path == 0 && dtype == PP_BF16 && k_attn_bwd_mfma(st, qkv, o, lse, dO, dqkv, Dbuf, B, S, h, dh, nullptr, nullptr) == 0))
+  if (!(path == 0 && ((dtype == PP_BF16 && k_attn_bwd_mfma(st, qkv, o, lse, dO, dqkv, Dbuf, B, S, h, dh, nullptr, nullptr) == 0) ||
+                      k_attn_bwd_f32(st, dtype, qkv, o, lse, dO, dqkv, Dbuf, B, S, h, dh) == 0)))
     k_attn_bwd_plain(st, dtype, qkv, o, lse, dO, dqkv, Dbuf, B, S, h, dh);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PP_EHIP, std::string("pp_op_attention_bwd: ") + hipGetErrorString(e));

@@ -67,6 +67,12 @@ void k_attn_D(hipStream_t st, int dtype, const void* o, const void* dO, float* D
 void k_attn_bwd_plain(hipStream_t st, int dtype, const void* qkv, const void* o, const float* lse, const void* dO, void* dqkv,
                       float* Dbuf, int B, int S, int h, int dh);
 
+// Attention in fp32 multiplies on the matrix cores (head dims 16, 32, 64, 128; fp32 or bf16 storage), the plain kernels' bits.
+// Return 0 if launched, 1 if the shape is not taken (nothing launched).  Dbuf receives rowsum(dO * O).
+int k_attn_fwd_f32(hipStream_t st, int dtype, const void* qkv, void* o, float* lse, int B, int S, int h, int dh);
+int k_attn_bwd_f32(hipStream_t st, int dtype, const void* qkv, const void* o, const float* lse, const void* dO, void* dqkv, float* Dbuf,
+                   int B, int S, int h, int dh);
+
 void k_embed_grad(hipStream_t st, int dtype, const int32_t* tok, const void* dx, float* gE, int T, int d, int V, int32_t* scratch);
 
 void k_pack_master(hipStream_t st, int dtype, const void* params, const RowInfo* rows, float* p, int n_rows, int d);

@@ -1,0 +1,55 @@
+"""fp32-multiply MFMA attention (fp32 models, bf16 head dims 16 and 32) against the plain kernels: the same sums in the same
+order, so the same bits, at the edges of its 32-query blocks, 128-key chunks and LDS limit, and with values that are not finite."""
+import numpy as np
+import pytest
+import torch
+
+import pp_inputs as gen
+import paper_2509_22418_amd as pp
+
+pytestmark = pytest.mark.gpu
+
+# (B, S, h, dh): single positions, one short of / past a block, past a chunk, the last length whose scores fit LDS and the first that does not
+CASES = [(1025, 1, 1, 16), (12, 31, 3, 32), (1, 33, 2, 64), (2, 128, 1, 128), (1, 161, 3, 16), (1, 257, 2, 128), (1, 1152, 1, 32), (1, 1153, 1, 64)]
+
+
+def run(qkv, dO, B, S, h, dh, dt, path):
+    st, d = torch.cuda.current_stream().cuda_stream, h * dh
+    o = torch.zeros((B * S, d), dtype=qkv.dtype, device="cuda")
+    lse, rows = (torch.zeros(B * h * S, dtype=torch.float32, device="cuda") for _ in range(2))
+    dqkv = torch.zeros((B * S, 3 * d), dtype=qkv.dtype, device="cuda")
+    pp.pp_op_attention_fwd(st, dt, qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), None, B, S, h, dh, path)
+    pp.pp_op_attention_bwd(st, dt, qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), dO.data_ptr(), dqkv.data_ptr(), rows.data_ptr(), None, B, S, h, dh, path)
+    torch.cuda.synchronize()
+    return o, lse, dqkv, rows
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,S,h,dh", CASES)
+def test_same_bits_as_the_plain_kernels(B, S, h, dh, dtype):
+    print(f"case attention f32 B={B} S={S} h={h} dh={dh} {dtype}", flush=True)
+    if dtype == "bf16" and dh >= 64:
+        pytest.skip("taken by the bf16 kernels")
+    td, dt = (torch.bfloat16, pp.PP_BF16) if dtype == "bf16" else (torch.float32, pp.PP_F32)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    qkv = torch.randn((B * S, 3 * h * dh), device="cuda", generator=g).to(td)
+    dO = torch.randn((B * S, h * dh), device="cuda", generator=g).to(td)
+    for a, b in zip(run(qkv, dO, B, S, h, dh, dt, 0), run(qkv, dO, B, S, h, dh, dt, 1)):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_values_that_are_not_finite_stay_behind_the_mask(value):
+    """One position whose q, k, v and dO are not finite: earlier queries do not see it, later keys are not reached by it, and every
+    output equals the plain kernels' (NaN where they have NaN)."""
+    B, S, h, dh, at = 1, 150, 2, 32, 70
+    g = torch.Generator(device="cuda").manual_seed(4)
+    qkv = torch.randn((S, 3 * h * dh), device="cuda", generator=g)
+    dO = torch.randn((S, h * dh), device="cuda", generator=g)
+    qkv[at, 5::7] = value
+    dO[at, 3] = value
+    got, ref = run(qkv, dO, B, S, h, dh, pp.PP_F32, 0), run(qkv, dO, B, S, h, dh, pp.PP_F32, 1)
+    assert bool(torch.isfinite(ref[0][:at]).all()) and not bool(torch.isfinite(ref[0][at:]).all())
+    for a, b in zip(got, ref):
+        assert torch.equal(torch.isnan(a), torch.isnan(b))
+        assert torch.equal(torch.nan_to_num(a, nan=7.0), torch.nan_to_num(b, nan=7.0))
