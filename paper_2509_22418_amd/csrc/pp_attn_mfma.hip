@@ -166,27 +166,33 @@ __device__ __forceinline__ void causal_block_map(int id, int n_pairs, int n_blk,
 
 // ------------------------------------------------------------------------------------------ forward
 // B*h*ceil(S/128) workgroups (see causal_block_map), 256 threads: wave w owns queries q0 + 32w .. +31; KV tiles of 64 keys.
-template <int DH>
-__global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int S, int h,
+// SPLIT (grids that leave compute units idle, see the launcher): one workgroup of 512 threads per query block, heaviest blocks first; waves w
+// and w + 4 own the same queries and take the even and the odd KV tiles, each group with its own two stages, and their
+// accumulators are merged through LDS at the end (reference points aligned as between tiles): half the serial chain per block.
+template <int DH, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int S, int h,
                                                            int n_pairs, int n_blk) {
-  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8;
+  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8, G = SPLIT ? 2 : 1;
   constexpr int CH = 4;          // fragment reads (= MFMAs) per fence; divides 2 KS and 4 CT
-  extern __shared__ u32x4 lds[];
+  extern __shared__ u32x4 lds_all[];
   constexpr int K_CH = 64 * CPRK, ST_CH = 2 * K_CH;          // a stage = K rows, then V rows, of 64 keys
   const int d = h * DH, ld = 3 * d;
   int pair, comb;
-  causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
+  if constexpr (SPLIT) { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }
+  else causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
   const int head = pair % h, b = pair / h;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, lh = lane >> 5;
+  const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3, grp = SPLIT ? wave8 >> 2 : 0;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  u32x4* const lds = lds_all + grp * 2 * ST_CH;
   const uint32_t tr_off = tr_lane_off<CPRK>(lane);
   // a late (heavy) query block, then its early (light) mirror image: every workgroup costs the same
-  for (int part = 0; part < 2; ++part) {
+  for (int part = 0; part < (SPLIT ? 1 : 2); ++part) {
     const int qblk = part == 0 ? n_blk - 1 - comb : comb;
     if (part == 1 && qblk == n_blk - 1 - comb) break;
     const int q0 = qblk * 128, qw0 = q0 + wave * 32;
     const int q = qw0 + l32;
     const bf16_t* base = qkv + (size_t)b * S * ld + (size_t)head * DH;
-    const int n_tiles = min((q0 + 128 + 63) / 64, (S + 63) / 64);
+    const int n_tiles = min((q0 + 128 + 63) / 64, (S + 63) / 64), n_it = (n_tiles + G - 1) / G;
 
     bf16x8 qf[KS];
     {
@@ -202,19 +208,20 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16_t* __restri
 
     auto ksrc = [&](int kv0) { return [=](int row, int c) { return base + (size_t)min(kv0 + row, S - 1) * ld + d + c * 8; }; };
     auto vsrc = [&](int kv0) { return [=](int row, int c) { return base + (size_t)min(kv0 + row, S - 1) * ld + 2 * d + c * 8; }; };
-    Stage<64, CPRK>::issue(lds, wave, lane, ksrc(0));
-    Stage<64, CPRK>::issue(lds + K_CH, wave, lane, vsrc(0));
+    Stage<64, CPRK>::issue(lds, wave, lane, ksrc(min(grp, n_tiles - 1) * 64));
+    Stage<64, CPRK>::issue(lds + K_CH, wave, lane, vsrc(min(grp, n_tiles - 1) * 64));
     stage_sync();
 
-    for (int j = 0; j < n_tiles; ++j) {
-      const u32x4* kt = lds + (j & 1) * ST_CH;
+    for (int it = 0; it < n_it; ++it) {
+      const int j = it * G + grp;
+      const u32x4* kt = lds + (it & 1) * ST_CH;
       const u32x4* vtile = kt + K_CH;
-      u32x4* nxt = lds + ((j + 1) & 1) * ST_CH;
-      const int kv0 = j * 64, kvn = min(j + 1, n_tiles - 1) * 64;
+      u32x4* nxt = lds + ((it + 1) & 1) * ST_CH;
+      const int kv0 = j * 64, kvn = min(j + G, n_tiles - 1) * 64;
       Stage<64, CPRK>::issue(nxt, wave, lane, ksrc(kvn));
       Stage<64, CPRK>::issue(nxt + K_CH, wave, lane, vsrc(kvn));
       __builtin_amdgcn_sched_barrier(0);
-      if (kv0 <= qw0 + 31) {          // wave-uniform: some key of the tile is visible to some query of this wave
+      if (kv0 <= qw0 + 31 && (!SPLIT || j < n_tiles)) {          // wave-uniform: some key of the tile is visible to some query of this wave
         f32x16 sacc[2];
         zero16(sacc[0]); zero16(sacc[1]);
         // MFMA steps n = 0 .. 2 KS - 1: key rows (n & 1) * 32.., head-dim slice n >> 1; CH steps per fence
@@ -305,7 +312,27 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16_t* __restri
       __builtin_amdgcn_sched_barrier(0);
       stage_sync();
     }
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    if constexpr (SPLIT) {          // (the loop's last barrier: nobody reads the stages any more and nothing is in flight into them)
+      float* mg = reinterpret_cast<float*>(lds_all) + wave * 64 * (16 * CT + 2) + lane;
+      if (grp == 1) {
+        mg[0] = m_run; mg[64] = l_tot;
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mg[(2 + c * 16 + r) * 64] = oacc[c][r];
+      }
+      __syncthreads();
+      if (grp == 1) return;
+      const float m1 = mg[0], l1 = mg[64], m = fmaxf(m_run, m1);          // m_run is finite for every query that exists: tile 0 has a visible key
+      const float a0 = fast_exp2(m_run - m), a1 = fast_exp2(m1 - m);
+      l_tot = l_tot * a0 + l1 * a1;
+      m_run = m;
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[c][r] = oacc[c][r] * a0 + mg[(2 + c * 16 + r) * 64] * a1;
+    }
     if (q < S) {
       const float inv = 1.0f / l_tot;
       bf16_t* op = o + ((size_t)b * S + q) * d + (size_t)head * DH + 4 * lh;
@@ -354,28 +381,33 @@ __device__ __forceinline__ void unrotate_tile(f32x16 (&acc)[DH / 32], const floa
 // S^T = K Q^T, dP^T = V dO^T, dS^T = P^T * (dP^T - D), dQ^T += K^T dS^T (K^T gathered from the K rows by transpose reads).
 // The kernel also forms D = rowsum(dO * O) for its queries (each lane already holds half of its query's dO row) and
 // stores it in Dbuf for the dK/dV kernel, which runs after it.
-template <int DH>
+// SPLIT (grids that leave compute units idle): 128 queries per workgroup, unpaired, heaviest first; waves w and w + 4 own the same queries and
+// take the even and the odd KV tiles with two stages of their own; the two accumulators are added through LDS.
+template <int DH, bool SPLIT>
 __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                               const bf16_t* __restrict__ dO, const float* __restrict__ lse,
                                                               float* __restrict__ Dbuf, bf16_t* __restrict__ dqkv, int S, int h, int n_pairs, int n_blk,
                                                               const float* __restrict__ cosb, const float* __restrict__ sinb) {
-  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8, NW = 8;
-  extern __shared__ u32x4 lds[];
+  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8, G = SPLIT ? 2 : 1, NW = 8 / G, QB = 32 * NW;
+  extern __shared__ u32x4 lds_all[];
   constexpr int K_CH = 64 * CPRK, ST_CH = 2 * K_CH;          // a stage = K rows, then V rows, of 64 keys
   const int d = h * DH, ld = 3 * d;
   int pair, comb;
-  causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
+  if constexpr (SPLIT) { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }
+  else causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
   const int head = pair % h, b = pair / h;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, lh = lane >> 5;
+  const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & (NW - 1), grp = SPLIT ? wave8 >> 2 : 0;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  u32x4* const lds = lds_all + grp * 2 * ST_CH;
   const uint32_t tr_off = tr_lane_off<CPRK>(lane);
   // a late (heavy) query block, then its early (light) mirror image: every workgroup costs the same
-  for (int part = 0; part < 2; ++part) {
+  for (int part = 0; part < (SPLIT ? 1 : 2); ++part) {
     const int qblk = part == 0 ? n_blk - 1 - comb : comb;
     if (part == 1 && qblk == n_blk - 1 - comb) break;
-    const int q0 = qblk * 256, qw0 = q0 + wave * 32;
+    const int q0 = qblk * QB, qw0 = q0 + wave * 32;
     const int q = qw0 + l32, qc = min(q, S - 1);
     const bf16_t* base = qkv + (size_t)b * S * ld + (size_t)head * DH;
-    const int n_tiles = min((q0 + 256 + 63) / 64, (S + 63) / 64);
+    const int n_tiles = min((q0 + QB + 63) / 64, (S + 63) / 64), n_it = (n_tiles + G - 1) / G;
     const float scale = 1.0f / sqrtf((float)DH), sc2 = LOG2E * scale;
 
     bf16x8 qf[KS], dof[KS];
@@ -398,7 +430,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __res
     }
     Dq += __shfl_xor(Dq, 32, 64);
     const size_t stat = ((size_t)b * h + head) * S + qc;
-    if (lh == 0 && q < S) Dbuf[stat] = Dq;
+    if (lh == 0 && q < S && grp == 0) Dbuf[stat] = Dq;
     const float nlse2 = -lse[stat] * LOG2E;
     f32x16 dqacc[CT];
 #pragma unroll
@@ -410,20 +442,21 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __res
       Stage<64, CPRK, NW>::issue(stage, wave, lane, ksrc(kv0));
       Stage<64, CPRK, NW>::issue(stage + K_CH, wave, lane, vsrc(kv0));
     };
-    issue_all(lds, 0);
+    issue_all(lds, min(grp, n_tiles - 1) * 64);
     stage_sync();
 
-    for (int j = 0; j < n_tiles; ++j) {
-      const u32x4* ktile = lds + (j & 1) * ST_CH;
+    for (int it = 0; it < n_it; ++it) {
+      const int j = it * G + grp;
+      const u32x4* ktile = lds + (it & 1) * ST_CH;
       const u32x4* vtile = ktile + K_CH;
-      u32x4* nxt = lds + ((j + 1) & 1) * ST_CH;
-      const int kv0 = j * 64, kvn = min(j + 1, n_tiles - 1) * 64;
+      u32x4* nxt = lds + ((it + 1) & 1) * ST_CH;
+      const int kv0 = j * 64, kvn = min(j + G, n_tiles - 1) * 64;
       issue_all(nxt, kvn);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {
         const int kg0 = kv0 + 32 * mt;
-        if (kg0 > qw0 + 31) continue;          // wave-uniform: every key of the group lies beyond every query of this wave
+        if (kg0 > qw0 + 31 || (SPLIT && j >= n_tiles)) continue;          // wave-uniform: every key of the group lies beyond every query of this wave
         f32x16 sacc, dpacc;
         zero16(sacc); zero16(dpacc);
         {
@@ -480,6 +513,21 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __res
       }
       __builtin_amdgcn_sched_barrier(0);
       stage_sync();
+    }
+    if constexpr (SPLIT) {          // (the loop's last barrier: the stages are free)
+      float* mg = reinterpret_cast<float*>(lds_all) + wave * 64 * 16 * CT + lane;
+      if (grp == 1) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mg[(c * 16 + r) * 64] = dqacc[c][r];
+      }
+      __syncthreads();
+      if (grp == 1) return;
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dqacc[c][r] += mg[(c * 16 + r) * 64];
     }
     if (q < S) {
       unrotate_tile<DH>(dqacc, cosb, sinb, q, lh);          // dQ w.r.t. the un-rotated query (linear: commutes with the scale below)
@@ -683,15 +731,16 @@ __device__ __forceinline__ void attn_bwd_dkv_part(u32x4* lds, const bf16_t* __re
 template <int DH>
 __global__ __launch_bounds__(512, 2) void attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO,
                                                                const float* __restrict__ lse, const float* __restrict__ Dbuf,
-                                                               bf16_t* __restrict__ dqkv, int S, int h, int n_pairs, int n_blk,
+                                                               bf16_t* __restrict__ dqkv, int S, int h, int n_pairs, int n_blk, int paired,
                                                                const float* __restrict__ cosb, const float* __restrict__ sinb) {
   extern __shared__ u32x4 lds[];
   int pair, comb;
-  causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
+  if (paired) causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
+  else { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }          // one block per workgroup, heaviest first
   const int head = pair % h, b = pair / h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // an early (heavy: it sees the most queries) key block, then its late (light) mirror image: every workgroup costs the same
-  for (int part = 0; part < 2; ++part) {
+  for (int part = 0; part <= paired; ++part) {
     const int kblk = part == 0 ? comb : n_blk - 1 - comb;
     if (part == 1 && kblk == comb) break;
     if (wave >= 4) attn_bwd_dkv_part<DH, true>(lds, qkv, dO, lse, Dbuf, dqkv, S, h, head, b, kblk, lane, wave, cosb, sinb);
@@ -705,28 +754,50 @@ static bool set_lds(K kern, int bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
 }
 
+// Pairing a heavy and a light block makes equal workgroups, which is what a full chip wants; a grid that does not fill it is as slow as
+// its longest workgroup, so there the blocks go out one by one, heaviest first, and the forward and dQ kernels split a
+// block's KV tiles over two groups of waves.  The line is where the single blocks no longer fit the chip at once (256 units; at head dim 64 two
+// workgroups each), moved up for long rows, whose chain weighs more than a second round's start-up.
+// us, paired / split, forward and backward (B x S, heads x dh): 3 x 777, 12 x 64 20.9 + 68 / 13.5 + 41; 2 x 2048, 12 x 64 36.8 + 113 / 26.5 + 82;
+// 1 x 2048, 16 x 128 50 + 174 / 38 + 119; 2 x 2048, 16 x 128 57 + 183 / 49 + 155; 8 x 300, 4 x 128 16 + 55 / 11 + 33; the other way round
+// 8 x 512, 16 x 128 (512 blocks of 4 tiles' chain) forward 25.6 / 28.8; 8 x 512, 24 x 64 (768) 23.2 + 76.9 / 23.7 + 79.7; 8 x 256, 32 x 64 backward 36.3 / 38.7.
 template <int DH>
 static int fwd_launch(hipStream_t st, const void* qkv, void* o, float* lse, int B, int S, int h) {
   constexpr int FWD_LDS = 2 * (2 * 64 * (DH / 8)) * 16;          // two stages of K rows + V rows
-  static bool ok = set_lds(attn_fwd_kernel<DH>, FWD_LDS);
+  constexpr int MERGE = 4 * 64 * (16 * (DH / 32) + 2) * 4;
+  constexpr int SPLIT_LDS = 2 * FWD_LDS > MERGE ? 2 * FWD_LDS : MERGE;
+  static bool ok = set_lds(attn_fwd_kernel<DH, false>, FWD_LDS) && set_lds(attn_fwd_kernel<DH, true>, SPLIT_LDS);
   if (!ok) return 1;
   const int n_blk = (S + 127) / 128;
-  attn_fwd_kernel<DH><<<dim3(B * h * ((n_blk + 1) / 2)), 256, FWD_LDS, st>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, h, B * h, n_blk);
+  const long paired = (long)B * h * ((n_blk + 1) / 2);
+  const long single = (long)B * h * n_blk;
+  if (n_blk > 1 && (single <= (DH == 64 ? 512 : 256) || (single <= (DH == 64 ? 768 : 512) && n_blk >= (DH == 64 ? 6 : 8))))
+    attn_fwd_kernel<DH, true><<<dim3(B * h * n_blk), 512, SPLIT_LDS, st>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, h, B * h, n_blk);
+  else
+    attn_fwd_kernel<DH, false><<<dim3((unsigned)paired), 256, FWD_LDS, st>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, h, B * h, n_blk);
   return 0;
 }
 template <int DH>
 static int bwd_launch(hipStream_t st, const void* qkv, const void* o, const float* lse, const void* dO, void* dqkv, float* Dbuf,
                       int B, int S, int h, const float* cosb, const float* sinb) {
   constexpr int DQ_LDS = 2 * (2 * 64 * (DH / 8)) * 16;                                   // two stages of K rows + V rows
+  constexpr int SPLIT_LDS = 2 * DQ_LDS;                                                  // for each of the two groups of waves (the merge needs half of it)
   constexpr int DKV_LDS = (3 * (2 * 64 * (DH / 8)) + 2 * (2 * 4 * 2 * 64) + 3 * 32) * 16;          // three sets of Q rows + dO rows, two P mailboxes, three sets of statistics
-  static bool ok = set_lds(attn_bwd_dq_kernel<DH>, DQ_LDS) && set_lds(attn_bwd_dkv_kernel<DH>, DKV_LDS);
+  static bool ok = set_lds(attn_bwd_dq_kernel<DH, false>, DQ_LDS) && set_lds(attn_bwd_dq_kernel<DH, true>, SPLIT_LDS) && set_lds(attn_bwd_dkv_kernel<DH>, DKV_LDS);
   if (!ok) return 1;
   const int nb_kv = (S + 127) / 128, nb_dq = (S + 255) / 256;
+  const long paired_dq = (long)B * h * ((nb_dq + 1) / 2), paired_kv = (long)B * h * ((nb_kv + 1) / 2);
   // the dQ kernel also writes D = rowsum(dO * O), which the dK/dV kernel then reads
-  attn_bwd_dq_kernel<DH><<<dim3(B * h * ((nb_dq + 1) / 2)), 512, DQ_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h,
-                                                                 B * h, nb_dq, cosb, sinb);
-  attn_bwd_dkv_kernel<DH><<<dim3(B * h * ((nb_kv + 1) / 2)), 512, DKV_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)dO, lse, Dbuf,
-                                                      (bf16_t*)dqkv, S, h, B * h, nb_kv, cosb, sinb);
+  const long single = (long)B * h * nb_kv;
+  if (nb_kv > 1 && paired_dq < 256 && (single <= 512 || (DH == 64 && single <= 768 && nb_kv >= 6)))
+    attn_bwd_dq_kernel<DH, true><<<dim3(B * h * nb_kv), 512, SPLIT_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h,
+                                                                              B * h, nb_kv, cosb, sinb);
+  else
+    attn_bwd_dq_kernel<DH, false><<<dim3((unsigned)paired_dq), 512, DQ_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h,
+                                                                                  B * h, nb_dq, cosb, sinb);
+  const int pair_kv = paired_kv >= 256;
+  attn_bwd_dkv_kernel<DH><<<dim3((unsigned)(pair_kv ? paired_kv : (long)B * h * nb_kv)), 512, DKV_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)dO, lse, Dbuf,
+                                                      (bf16_t*)dqkv, S, h, B * h, nb_kv, pair_kv, cosb, sinb);
   return 0;
 }
 
