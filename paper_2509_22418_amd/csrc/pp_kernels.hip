@@ -922,78 +922,102 @@ __global__ void embed_grad_kernel(const int32_t* __restrict__ tok, const T* __re
   }
 }
 // The same sums in the same order without every row scanning every token: positions are ranked by (token, position) --
-// one thread per position counts the positions with a smaller token and the earlier ones with its own token, T^2 / 2
-// comparisons from LDS -- which yields the position list of every token, in position order, as a segment of one array.
+// T^2 comparisons from LDS count the positions with a smaller token and the earlier ones with the same token -- which yields the
+// position list of every token, in position order, as a segment of one array.
 // idx: [T] sorted positions, then [V] segment starts, then [V] segment lengths (lengths zeroed beforehand).
-__global__ __launch_bounds__(64) void embed_rank_kernel(const int32_t* __restrict__ tok, int32_t* __restrict__ idx, int T_, int V) {
-  __shared__ int32_t chunk[1024];
-  const int t = blockIdx.x * 64 + threadIdx.x;
+// Bound by the comparisons: a workgroup ranks 64 positions with 16 waves, each scanning a sixteenth of every 4096-token
+// chunk by 16-byte broadcast reads, four instructions per comparison pair.  (One wave per 64 positions took 250 us for 8192 tokens, a fiftieth of the whole step; now under 15.)
+__global__ __launch_bounds__(1024) void embed_rank_kernel(const int32_t* __restrict__ tok, int32_t* __restrict__ idx, int T_, int V) {
+  constexpr int CHUNK = 4096, PER = CHUNK / 16;
+  __shared__ int4 chunk[CHUNK / 4];
+  __shared__ int32_t cnt[16][3][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b0 = blockIdx.x * 64, t = b0 + lane;
   const int my = t < T_ ? tok[t] : -1;
   int less = 0, eq_before = 0, eq_total = 0;
-  for (int t0 = 0; t0 < T_; t0 += 1024) {
+  for (int t0 = 0; t0 < T_; t0 += CHUNK) {
     __syncthreads();
-    for (int i = threadIdx.x; i < 1024; i += 64) chunk[i] = t0 + i < T_ ? tok[t0 + i] : 0x7fffffff;
+    for (int i = threadIdx.x; i < CHUNK; i += 1024) reinterpret_cast<int32_t*>(chunk)[i] = t0 + i < T_ ? tok[t0 + i] : 0x7fffffff;
     __syncthreads();
-    const int n = min(1024, T_ - t0);
-    for (int i = 0; i < n; ++i) {
-      const int o = chunk[i];
-      less += o < my;
-      eq_total += o == my;
-      eq_before += (o == my) & (t0 + i < t);
+    const int w0 = t0 + wave * PER;          // this wave's part of the chunk: positions w0 .. w0 + PER - 1
+    int eq = 0;
+    if (w0 + PER <= b0 || w0 >= b0 + 64) {          // wholly before or wholly after the block's positions
+#pragma unroll 4
+      for (int i = 0; i < PER / 4; ++i) {
+        const int4 o = chunk[wave * (PER / 4) + i];
+        less += (o.x < my) + (o.y < my) + (o.z < my) + (o.w < my);
+        eq += (o.x == my) + (o.y == my) + (o.z == my) + (o.w == my);
+      }
+      if (w0 < b0) eq_before += eq;
+    } else {
+      for (int i = 0; i < PER; ++i) {
+        const int o = reinterpret_cast<const int32_t*>(chunk)[wave * PER + i];
+        less += o < my;
+        eq += o == my;
+        eq_before += (o == my) & (w0 + i < t);
+      }
     }
+    eq_total += eq;
   }
-  if (t >= T_ || my < 0 || my >= V) return;          // tokens outside the vocabulary contribute nothing (as in the forward gather's clamp-free contract)
+  cnt[wave][0][lane] = less; cnt[wave][1][lane] = eq_before; cnt[wave][2][lane] = eq_total;
+  __syncthreads();
+  if (wave > 0 || t >= T_ || my < 0 || my >= V) return;          // tokens outside the vocabulary contribute nothing (as in the forward gather's clamp-free contract)
+  for (int w = 1; w < 16; ++w) { less += cnt[w][0][lane]; eq_before += cnt[w][1][lane]; eq_total += cnt[w][2][lane]; }
   idx[less + eq_before] = t;
   if (eq_before == 0) { idx[T_ + my] = less; idx[T_ + V + my] = eq_total; }
 }
-// One block per vocabulary row, 256 threads = 4 hit lanes x 64 column lanes.  Hit lane j sums the row's positions
-// j, j+4, j+8, ... (in that order) for 16-byte column pieces, four loads in flight; the four partial sums are then added in
-// the order ((0 + 1) + 2) + 3.  The order is fixed, so the result does not depend on scheduling; a frequent token (the
-// synthetic tokens are Zipf distributed: the commonest one takes a tenth of the positions) costs a quarter of its count in
-// dependent steps instead of all of it.
+// One block per vocabulary row and piece of 64 x 16 bytes of columns, 256 threads = 4 hit lanes x 64 column lanes.  Hit lane j sums the
+// row's positions j, j+4, j+8, ... (in that order), eight loads in flight; the four partial sums are then added in
+// the order ((0 + 1) + 2) + 3.  The order is fixed, so the result does not depend on scheduling.  Two things bound it: writing V x d
+// floats, most of them zeros of rows without a position (16-byte stores), and the row of the commonest token (the synthetic tokens are
+// Zipf distributed: a tenth of the positions), whose chain is one block per column piece.  (All column pieces in turn in one block, four loads
+// in flight, 4-byte stores: 296 us for 32000 x 2048 and 8192 positions, now 99.)
 template <class T>
 __global__ __launch_bounds__(256) void embed_grad_sorted_kernel(const int32_t* __restrict__ idx, const T* __restrict__ dx, float* __restrict__ gE, int T_, int d, int V) {
   constexpr int VEC = 16 / sizeof(T);          // elements per 16-byte piece
-  __shared__ float part[3][64 * VEC];
-  const int v = blockIdx.x;
+  __shared__ __align__(16) float part[3][64 * VEC];
+  const int v = blockIdx.x, c0 = blockIdx.y * 64 * VEC;
   const int nh = idx[T_ + V + v], s0 = nh ? idx[T_ + v] : 0;
   const int hl = threadIdx.x >> 6, cl = threadIdx.x & 63;
   float* out = gE + (size_t)v * d;
-  for (int c0 = 0; c0 < d; c0 += 64 * VEC) {          // uniform trip count: the barriers below are reached by every thread
-    const int c = c0 + cl * VEC;
-    float acc[VEC];
+  if (nh == 0) {          // d is a multiple of 4, rows start 16-byte aligned
+    for (int c = c0 + threadIdx.x * 4; c < min(d, c0 + 64 * VEC); c += 1024) *reinterpret_cast<float4*>(out + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+    return;
+  }
+  const int c = c0 + cl * VEC;
+  float acc[VEC];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-    if (c < d) {
-      int k = hl;
-      for (; k + 12 < nh; k += 16) {          // four independent loads in flight
-        uint4 w[4];
+  for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+  if (c < d) {
+    int k = hl;
+    for (; k + 28 < nh; k += 32) {          // eight independent loads in flight
+      uint4 w[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) w[u] = *reinterpret_cast<const uint4*>(dx + (size_t)idx[s0 + k + 4 * u] * d + c);
+      for (int u = 0; u < 8; ++u) w[u] = *reinterpret_cast<const uint4*>(dx + (size_t)idx[s0 + k + 4 * u] * d + c);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const T* pv = reinterpret_cast<const T*>(&w[u]);
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) acc[e] += to_f32(pv[e]);
-        }
-      }
-      for (; k < nh; k += 4) {
-        const uint4 w = *reinterpret_cast<const uint4*>(dx + (size_t)idx[s0 + k] * d + c);
-        const T* pv = reinterpret_cast<const T*>(&w);
+      for (int u = 0; u < 8; ++u) {
+        const T* pv = reinterpret_cast<const T*>(&w[u]);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) acc[e] += to_f32(pv[e]);
       }
     }
-    __syncthreads();          // the previous piece's partials have been read
-    if (hl > 0) {
+    for (; k < nh; k += 4) {
+      const uint4 w = *reinterpret_cast<const uint4*>(dx + (size_t)idx[s0 + k] * d + c);
+      const T* pv = reinterpret_cast<const T*>(&w);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) part[hl - 1][cl * VEC + e] = acc[e];
+      for (int e = 0; e < VEC; ++e) acc[e] += to_f32(pv[e]);
     }
-    __syncthreads();
-    if (hl == 0 && c < d) {
+  }
+  if (hl > 0) {
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) out[c + e] = ((acc[e] + part[0][cl * VEC + e]) + part[1][cl * VEC + e]) + part[2][cl * VEC + e];
-    }
+    for (int e = 0; e < VEC; ++e) part[hl - 1][cl * VEC + e] = acc[e];
+  }
+  __syncthreads();
+  if (hl == 0 && c < d) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] = ((acc[e] + part[0][cl * VEC + e]) + part[1][cl * VEC + e]) + part[2][cl * VEC + e];
+#pragma unroll
+    for (int e = 0; e < VEC; e += 4) *reinterpret_cast<float4*>(out + c + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
   }
 }
 // scratch: (T + 2 V) ints of device memory that nothing else uses during the call, or nullptr (then every row scans the tokens)
@@ -1004,8 +1028,8 @@ void k_embed_grad(hipStream_t st, int dtype, const int32_t* tok, const void* dx,
     return;
   }
   k_fill_f32(st, reinterpret_cast<float*>(scratch + T_ + V), (size_t)V, 0.f);          // segment lengths := 0 (all-zero bits)
-  embed_rank_kernel<<<cdiv(T_, 64), 64, 0, st>>>(tok, scratch, T_, V);
-  PP_DISPATCH(dtype, embed_grad_sorted_kernel<T><<<V, 256, 0, st>>>(scratch, (const T*)dx, gE, T_, d, V));
+  embed_rank_kernel<<<cdiv(T_, 64), 1024, 0, st>>>(tok, scratch, T_, V);
+  PP_DISPATCH(dtype, embed_grad_sorted_kernel<T><<<dim3(V, cdiv(d, 64 * vec)), 256, 0, st>>>(scratch, (const T*)dx, gE, T_, d, V));
 }
 
 // ------------------------------------------------------------------------------------------ packed-subset kernels
