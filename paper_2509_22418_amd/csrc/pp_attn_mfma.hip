@@ -166,33 +166,28 @@ __device__ __forceinline__ void causal_block_map(int id, int n_pairs, int n_blk,
 
 // ------------------------------------------------------------------------------------------ forward
 // B*h*ceil(S/128) workgroups (see causal_block_map), 256 threads: wave w owns queries q0 + 32w .. +31; KV tiles of 64 keys.
-// SPLIT (grids that leave compute units idle, see the launcher): one workgroup of 512 threads per query block, heaviest blocks first; waves w
-// and w + 4 own the same queries and take the even and the odd KV tiles, each group with its own two stages, and their
-// accumulators are merged through LDS at the end (reference points aligned as between tiles): half the serial chain per block.
-template <int DH, bool SPLIT>
-__global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int S, int h,
+template <int DH, bool PAIRED>
+__global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int S, int h,
                                                            int n_pairs, int n_blk) {
-  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8, G = SPLIT ? 2 : 1;
+  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8;
   constexpr int CH = 4;          // fragment reads (= MFMAs) per fence; divides 2 KS and 4 CT
-  extern __shared__ u32x4 lds_all[];
+  extern __shared__ u32x4 lds[];
   constexpr int K_CH = 64 * CPRK, ST_CH = 2 * K_CH;          // a stage = K rows, then V rows, of 64 keys
   const int d = h * DH, ld = 3 * d;
   int pair, comb;
-  if constexpr (SPLIT) { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }
-  else causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
+  if constexpr (PAIRED) causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
+  else { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }          // one block per workgroup, heaviest first
   const int head = pair % h, b = pair / h;
-  const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3, grp = SPLIT ? wave8 >> 2 : 0;
-  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
-  u32x4* const lds = lds_all + grp * 2 * ST_CH;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, lh = lane >> 5;
   const uint32_t tr_off = tr_lane_off<CPRK>(lane);
   // a late (heavy) query block, then its early (light) mirror image: every workgroup costs the same
-  for (int part = 0; part < (SPLIT ? 1 : 2); ++part) {
+  for (int part = 0; part < (PAIRED ? 2 : 1); ++part) {
     const int qblk = part == 0 ? n_blk - 1 - comb : comb;
     if (part == 1 && qblk == n_blk - 1 - comb) break;
     const int q0 = qblk * 128, qw0 = q0 + wave * 32;
     const int q = qw0 + l32;
     const bf16_t* base = qkv + (size_t)b * S * ld + (size_t)head * DH;
-    const int n_tiles = min((q0 + 128 + 63) / 64, (S + 63) / 64), n_it = (n_tiles + G - 1) / G;
+    const int n_tiles = min((q0 + 128 + 63) / 64, (S + 63) / 64);
 
     bf16x8 qf[KS];
     {
@@ -208,20 +203,19 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void attn_fwd_kernel(const bf
 
     auto ksrc = [&](int kv0) { return [=](int row, int c) { return base + (size_t)min(kv0 + row, S - 1) * ld + d + c * 8; }; };
     auto vsrc = [&](int kv0) { return [=](int row, int c) { return base + (size_t)min(kv0 + row, S - 1) * ld + 2 * d + c * 8; }; };
-    Stage<64, CPRK>::issue(lds, wave, lane, ksrc(min(grp, n_tiles - 1) * 64));
-    Stage<64, CPRK>::issue(lds + K_CH, wave, lane, vsrc(min(grp, n_tiles - 1) * 64));
+    Stage<64, CPRK>::issue(lds, wave, lane, ksrc(0));
+    Stage<64, CPRK>::issue(lds + K_CH, wave, lane, vsrc(0));
     stage_sync();
 
-    for (int it = 0; it < n_it; ++it) {
-      const int j = it * G + grp;
-      const u32x4* kt = lds + (it & 1) * ST_CH;
+    for (int j = 0; j < n_tiles; ++j) {
+      const u32x4* kt = lds + (j & 1) * ST_CH;
       const u32x4* vtile = kt + K_CH;
-      u32x4* nxt = lds + ((it + 1) & 1) * ST_CH;
-      const int kv0 = j * 64, kvn = min(j + G, n_tiles - 1) * 64;
+      u32x4* nxt = lds + ((j + 1) & 1) * ST_CH;
+      const int kv0 = j * 64, kvn = min(j + 1, n_tiles - 1) * 64;
       Stage<64, CPRK>::issue(nxt, wave, lane, ksrc(kvn));
       Stage<64, CPRK>::issue(nxt + K_CH, wave, lane, vsrc(kvn));
       __builtin_amdgcn_sched_barrier(0);
-      if (kv0 <= qw0 + 31 && (!SPLIT || j < n_tiles)) {          // wave-uniform: some key of the tile is visible to some query of this wave
+      if (kv0 <= qw0 + 31) {          // wave-uniform: some key of the tile is visible to some query of this wave
         f32x16 sacc[2];
         zero16(sacc[0]); zero16(sacc[1]);
         // MFMA steps n = 0 .. 2 KS - 1: key rows (n & 1) * 32.., head-dim slice n >> 1; CH steps per fence
@@ -312,27 +306,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void attn_fwd_kernel(const bf
       __builtin_amdgcn_sched_barrier(0);
       stage_sync();
     }
-    float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-    if constexpr (SPLIT) {          // (the loop's last barrier: nobody reads the stages any more and nothing is in flight into them)
-      float* mg = reinterpret_cast<float*>(lds_all) + wave * 64 * (16 * CT + 2) + lane;
-      if (grp == 1) {
-        mg[0] = m_run; mg[64] = l_tot;
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) mg[(2 + c * 16 + r) * 64] = oacc[c][r];
-      }
-      __syncthreads();
-      if (grp == 1) return;
-      const float m1 = mg[0], l1 = mg[64], m = fmaxf(m_run, m1);          // m_run is finite for every query that exists: tile 0 has a visible key
-      const float a0 = fast_exp2(m_run - m), a1 = fast_exp2(m1 - m);
-      l_tot = l_tot * a0 + l1 * a1;
-      m_run = m;
-#pragma unroll
-      for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[c][r] = oacc[c][r] * a0 + mg[(2 + c * 16 + r) * 64] * a1;
-    }
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
     if (q < S) {
       const float inv = 1.0f / l_tot;
       bf16_t* op = o + ((size_t)b * S + q) * d + (size_t)head * DH + 4 * lh;
@@ -383,7 +357,7 @@ __device__ __forceinline__ void unrotate_tile(f32x16 (&acc)[DH / 32], const floa
 // stores it in Dbuf for the dK/dV kernel, which runs after it.
 // SPLIT (grids that leave compute units idle): 128 queries per workgroup, unpaired, heaviest first; waves w and w + 4 own the same queries and
 // take the even and the odd KV tiles with two stages of their own; the two accumulators are added through LDS.
-template <int DH, bool SPLIT>
+template <int DH, bool SPLIT, bool PAIRED>          // SPLIT: not PAIRED
 __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                               const bf16_t* __restrict__ dO, const float* __restrict__ lse,
                                                               float* __restrict__ Dbuf, bf16_t* __restrict__ dqkv, int S, int h, int n_pairs, int n_blk,
@@ -393,7 +367,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __res
   constexpr int K_CH = 64 * CPRK, ST_CH = 2 * K_CH;          // a stage = K rows, then V rows, of 64 keys
   const int d = h * DH, ld = 3 * d;
   int pair, comb;
-  if constexpr (SPLIT) { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }
+  if constexpr (!PAIRED) { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }          // one block per workgroup, heaviest first
   else causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
   const int head = pair % h, b = pair / h;
   const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & (NW - 1), grp = SPLIT ? wave8 >> 2 : 0;
@@ -401,7 +375,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __res
   u32x4* const lds = lds_all + grp * 2 * ST_CH;
   const uint32_t tr_off = tr_lane_off<CPRK>(lane);
   // a late (heavy) query block, then its early (light) mirror image: every workgroup costs the same
-  for (int part = 0; part < (SPLIT ? 1 : 2); ++part) {
+  for (int part = 0; part < (PAIRED ? 2 : 1); ++part) {
     const int qblk = part == 0 ? n_blk - 1 - comb : comb;
     if (part == 1 && qblk == n_blk - 1 - comb) break;
     const int q0 = qblk * QB, qw0 = q0 + wave * 32;
@@ -728,19 +702,19 @@ __device__ __forceinline__ void attn_bwd_dkv_part(u32x4* lds, const bf16_t* __re
 
 // The two roles are separate instantiations of the tile loop (their loop-invariant registers differ); both cross the
 // same number of barriers.
-template <int DH>
+template <int DH, bool PAIRED>
 __global__ __launch_bounds__(512, 2) void attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO,
                                                                const float* __restrict__ lse, const float* __restrict__ Dbuf,
-                                                               bf16_t* __restrict__ dqkv, int S, int h, int n_pairs, int n_blk, int paired,
+                                                               bf16_t* __restrict__ dqkv, int S, int h, int n_pairs, int n_blk,
                                                                const float* __restrict__ cosb, const float* __restrict__ sinb) {
   extern __shared__ u32x4 lds[];
   int pair, comb;
-  if (paired) causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
+  if constexpr (PAIRED) causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
   else { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }          // one block per workgroup, heaviest first
   const int head = pair % h, b = pair / h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // an early (heavy: it sees the most queries) key block, then its late (light) mirror image: every workgroup costs the same
-  for (int part = 0; part <= paired; ++part) {
+  for (int part = 0; part < (PAIRED ? 2 : 1); ++part) {
     const int kblk = part == 0 ? comb : n_blk - 1 - comb;
     if (part == 1 && kblk == comb) break;
     if (wave >= 4) attn_bwd_dkv_part<DH, true>(lds, qkv, dO, lse, Dbuf, dqkv, S, h, head, b, kblk, lane, wave, cosb, sinb);
@@ -754,27 +728,24 @@ static bool set_lds(K kern, int bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
 }
 
-// Pairing a heavy and a light block makes equal workgroups, which is what a full chip wants; a grid that does not fill it is as slow as
-// its longest workgroup, so there the blocks go out one by one, heaviest first, and the forward and dQ kernels split a
-// block's KV tiles over two groups of waves.  The line is where the single blocks no longer fit the chip at once (256 units; at head dim 64 two
-// workgroups each), moved up for long rows, whose chain weighs more than a second round's start-up.
-// us, paired / split, forward and backward (B x S, heads x dh): 3 x 777, 12 x 64 20.9 + 68 / 13.5 + 41; 2 x 2048, 12 x 64 36.8 + 113 / 26.5 + 82;
-// 1 x 2048, 16 x 128 50 + 174 / 38 + 119; 2 x 2048, 16 x 128 57 + 183 / 49 + 155; 8 x 300, 4 x 128 16 + 55 / 11 + 33; the other way round
-// 8 x 512, 16 x 128 (512 blocks of 4 tiles' chain) forward 25.6 / 28.8; 8 x 512, 24 x 64 (768) 23.2 + 76.9 / 23.7 + 79.7; 8 x 256, 32 x 64 backward 36.3 / 38.7.
+// Pairing a heavy and a light block makes equal workgroups, which is what a full chip wants.  A grid whose last round is partly empty is as
+// slow as its longest workgroup, and single blocks, heaviest first, fill the gaps: paired only when the equal workgroups use at least 4 / 5 of
+// the slots of all their rounds (two forward workgroups of four waves, one dQ or dK/dV workgroup of eight waves per compute unit).  The order of a
+// row's sums does not depend on it.  us, paired / single, forward and backward: 8 x 1024, 12 heads of 64 (384, 192 and 384 paired workgroups on
+// 512, 256 and 256 slots) 33.4 + 109 / 27.6 + 100; 8 x 1000, 20 heads of 128 79.5 + 299 / 70.1 + 263; 8 x 512, 24 heads of 64 23.4 + 77 / 20.7 + 68.
+static int full_rounds(long wgs, long slots) { return 5 * wgs >= 4 * slots * ((wgs + slots - 1) / slots); }
+
 template <int DH>
 static int fwd_launch(hipStream_t st, const void* qkv, void* o, float* lse, int B, int S, int h) {
   constexpr int FWD_LDS = 2 * (2 * 64 * (DH / 8)) * 16;          // two stages of K rows + V rows
-  constexpr int MERGE = 4 * 64 * (16 * (DH / 32) + 2) * 4;
-  constexpr int SPLIT_LDS = 2 * FWD_LDS > MERGE ? 2 * FWD_LDS : MERGE;
-  static bool ok = set_lds(attn_fwd_kernel<DH, false>, FWD_LDS) && set_lds(attn_fwd_kernel<DH, true>, SPLIT_LDS);
+  static bool ok = set_lds(attn_fwd_kernel<DH, true>, FWD_LDS) && set_lds(attn_fwd_kernel<DH, false>, FWD_LDS);
   if (!ok) return 1;
   const int n_blk = (S + 127) / 128;
   const long paired = (long)B * h * ((n_blk + 1) / 2);
-  const long single = (long)B * h * n_blk;
-  if (n_blk > 1 && (single <= (DH == 64 ? 512 : 256) || (single <= (DH == 64 ? 768 : 512) && n_blk >= (DH == 64 ? 6 : 8))))
-    attn_fwd_kernel<DH, true><<<dim3(B * h * n_blk), 512, SPLIT_LDS, st>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, h, B * h, n_blk);
-  else
-    attn_fwd_kernel<DH, false><<<dim3((unsigned)paired), 256, FWD_LDS, st>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, h, B * h, n_blk);
+  // at head dim 128 a unit with one workgroup runs it a fifth faster than one of two: 256 equal ones are a full chip (1 x 4096, 16 heads: 95 us paired, 105 single)
+  const int pr = full_rounds(paired, DH == 128 && paired <= 256 ? 256 : 512);
+  auto kern = pr ? attn_fwd_kernel<DH, true> : attn_fwd_kernel<DH, false>;
+  kern<<<dim3((unsigned)(pr ? paired : (long)B * h * n_blk)), 256, FWD_LDS, st>>>((const bf16_t*)qkv, (bf16_t*)o, lse, S, h, B * h, n_blk);
   return 0;
 }
 template <int DH>
@@ -783,21 +754,29 @@ static int bwd_launch(hipStream_t st, const void* qkv, const void* o, const floa
   constexpr int DQ_LDS = 2 * (2 * 64 * (DH / 8)) * 16;                                   // two stages of K rows + V rows
   constexpr int SPLIT_LDS = 2 * DQ_LDS;                                                  // for each of the two groups of waves (the merge needs half of it)
   constexpr int DKV_LDS = (3 * (2 * 64 * (DH / 8)) + 2 * (2 * 4 * 2 * 64) + 3 * 32) * 16;          // three sets of Q rows + dO rows, two P mailboxes, three sets of statistics
-  static bool ok = set_lds(attn_bwd_dq_kernel<DH, false>, DQ_LDS) && set_lds(attn_bwd_dq_kernel<DH, true>, SPLIT_LDS) && set_lds(attn_bwd_dkv_kernel<DH>, DKV_LDS);
+  static bool ok = set_lds(attn_bwd_dq_kernel<DH, false, true>, DQ_LDS) && set_lds(attn_bwd_dq_kernel<DH, false, false>, DQ_LDS) &&
+                   set_lds(attn_bwd_dq_kernel<DH, true, false>, SPLIT_LDS) && set_lds(attn_bwd_dkv_kernel<DH, true>, DKV_LDS) && set_lds(attn_bwd_dkv_kernel<DH, false>, DKV_LDS);
   if (!ok) return 1;
   const int nb_kv = (S + 127) / 128, nb_dq = (S + 255) / 256;
   const long paired_dq = (long)B * h * ((nb_dq + 1) / 2), paired_kv = (long)B * h * ((nb_kv + 1) / 2);
-  // the dQ kernel also writes D = rowsum(dO * O), which the dK/dV kernel then reads
+  // the dQ kernel also writes D = rowsum(dO * O), which the dK/dV kernel then reads.
+  // Grids that leave compute units idle split the dQ blocks' KV tiles over two groups of waves; the line is where the single blocks no longer
+  // fit the chip in two rounds, moved up at head dim 64 for long rows, whose chain weighs more than another round's start-up.  us, whole backward,
+  // paired / split and single: 3 x 777, 12 x 64 68 / 41; 2 x 2048, 12 x 64 113 / 77; 1 x 2048, 16 x 128 174 / 116; 2 x 2048, 16 x 128 183 / 157; 8 x 300, 4 x 128
+  // 55 / 33; against it 8 x 512, 24 x 64 (768 blocks of at most 8 tiles) 76.9 / 79.7.  (The forward kernel is not split: its sums keep their order.)
   const long single = (long)B * h * nb_kv;
   if (nb_kv > 1 && paired_dq < 256 && (single <= 512 || (DH == 64 && single <= 768 && nb_kv >= 6)))
-    attn_bwd_dq_kernel<DH, true><<<dim3(B * h * nb_kv), 512, SPLIT_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h,
-                                                                              B * h, nb_kv, cosb, sinb);
-  else
-    attn_bwd_dq_kernel<DH, false><<<dim3((unsigned)paired_dq), 512, DQ_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h,
-                                                                                  B * h, nb_dq, cosb, sinb);
-  const int pair_kv = paired_kv >= 256;
-  attn_bwd_dkv_kernel<DH><<<dim3((unsigned)(pair_kv ? paired_kv : (long)B * h * nb_kv)), 512, DKV_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)dO, lse, Dbuf,
-                                                      (bf16_t*)dqkv, S, h, B * h, nb_kv, pair_kv, cosb, sinb);
+    attn_bwd_dq_kernel<DH, true, false><<<dim3(B * h * nb_kv), 512, SPLIT_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h,
+                                                                                     B * h, nb_kv, cosb, sinb);
+  else {
+    const int pr = full_rounds(paired_dq, 256);
+    auto kern = pr ? attn_bwd_dq_kernel<DH, false, true> : attn_bwd_dq_kernel<DH, false, false>;
+    kern<<<dim3((unsigned)(pr ? paired_dq : (long)B * h * nb_dq)), 512, DQ_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h, B * h, nb_dq,
+                                                                                      cosb, sinb);
+  }
+  const int pair_kv = full_rounds(paired_kv, 256);
+  auto kern = pair_kv ? attn_bwd_dkv_kernel<DH, true> : attn_bwd_dkv_kernel<DH, false>;
+  kern<<<dim3((unsigned)(pair_kv ? paired_kv : (long)B * h * nb_kv)), 512, DKV_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h, B * h, nb_kv, cosb, sinb);
   return 0;
 }
 

@@ -1,4 +1,4 @@
-"""bf16 attention at the edges of its work split: single query blocks with KV tiles dealt to two groups of waves (an odd tile count,
+"""bf16 attention at the edges of its work split: single blocks, dQ's KV tiles dealt to two groups of waves (an odd tile count,
 one row past a block, groups without a visible tile), and paired blocks once the grid fills the chip; against fp64."""
 import math
 
@@ -9,8 +9,8 @@ import paper_2509_22418_amd as pp
 
 pytestmark = pytest.mark.gpu
 
-# (B, S, h, dh): split (at most 256 / 512 blocks), then paired
-CASES = [(1, 129, 1, 64), (2, 191, 3, 128), (1, 321, 2, 64), (3, 777, 4, 64), (2, 640, 1, 128), (8, 257, 22, 64), (8, 257, 11, 128), (4, 1025, 13, 64), (4, 260, 64, 64)]
+# (B, S, h, dh): split, then single blocks, then paired
+CASES = [(1, 129, 1, 64), (2, 191, 3, 128), (1, 321, 2, 64), (3, 777, 4, 64), (2, 640, 1, 128), (8, 257, 22, 64), (8, 257, 11, 128), (4, 1025, 13, 64), (4, 260, 64, 64), (8, 257, 64, 128), (8, 140, 64, 64)]
 
 
 @pytest.mark.parametrize("B,S,h,dh", CASES)
