@@ -350,29 +350,29 @@ __device__ __forceinline__ void unrotate_tile(f32x16 (&acc)[DH / 32], const floa
 }
 
 // ------------------------------------------------------------------------------------------ backward: dQ
-// B*h*ceil(S/256) workgroups (see causal_block_map), 512 threads = 8 waves (2 per SIMD, <= 256 registers each, so every MFMA keeps its
-// accumulator in ordinary VGPRs): wave w owns queries q0 + 32w .. +31.  Per KV tile of 64 keys, in two groups of 32:
+// NW waves of 32 queries each (2 waves per SIMD, <= 256 registers, so every MFMA keeps its accumulator in ordinary VGPRs): wave w owns
+// queries q0 + 32w .. +31.  NW = 4: one block of 128 queries per workgroup, heaviest first, two workgroups per compute unit.  NW = 8: a heavy
+// block of 256 queries and its light mirror image per workgroup (see causal_block_map), which reads K and V half as often.  In both forms
+// a wave adds its KV tiles in ascending order, so the bits of a sequence and head do not depend on how many share the launch.
+// Per KV tile of 64 keys, in two groups of 32:
 // S^T = K Q^T, dP^T = V dO^T, dS^T = P^T * (dP^T - D), dQ^T += K^T dS^T (K^T gathered from the K rows by transpose reads).
 // The kernel also forms D = rowsum(dO * O) for its queries (each lane already holds half of its query's dO row) and
 // stores it in Dbuf for the dK/dV kernel, which runs after it.
-// SPLIT (grids that leave compute units idle): 128 queries per workgroup, unpaired, heaviest first; waves w and w + 4 own the same queries and
-// take the even and the odd KV tiles with two stages of their own; the two accumulators are added through LDS.
-template <int DH, bool SPLIT, bool PAIRED>          // SPLIT: not PAIRED
-__global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+template <int DH, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                               const bf16_t* __restrict__ dO, const float* __restrict__ lse,
                                                               float* __restrict__ Dbuf, bf16_t* __restrict__ dqkv, int S, int h, int n_pairs, int n_blk,
                                                               const float* __restrict__ cosb, const float* __restrict__ sinb) {
-  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8, G = SPLIT ? 2 : 1, NW = 8 / G, QB = 32 * NW;
-  extern __shared__ u32x4 lds_all[];
+  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8, QB = 32 * NW;
+  constexpr bool PAIRED = NW == 8;
+  extern __shared__ u32x4 lds[];
   constexpr int K_CH = 64 * CPRK, ST_CH = 2 * K_CH;          // a stage = K rows, then V rows, of 64 keys
   const int d = h * DH, ld = 3 * d;
   int pair, comb;
-  if constexpr (!PAIRED) { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }          // one block per workgroup, heaviest first
-  else causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
+  if constexpr (PAIRED) causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
+  else { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }          // one block per workgroup, heaviest first
   const int head = pair % h, b = pair / h;
-  const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & (NW - 1), grp = SPLIT ? wave8 >> 2 : 0;
-  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
-  u32x4* const lds = lds_all + grp * 2 * ST_CH;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, lh = lane >> 5;
   const uint32_t tr_off = tr_lane_off<CPRK>(lane);
   // a late (heavy) query block, then its early (light) mirror image: every workgroup costs the same
   for (int part = 0; part < (PAIRED ? 2 : 1); ++part) {
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __res
     const int q0 = qblk * QB, qw0 = q0 + wave * 32;
     const int q = qw0 + l32, qc = min(q, S - 1);
     const bf16_t* base = qkv + (size_t)b * S * ld + (size_t)head * DH;
-    const int n_tiles = min((q0 + QB + 63) / 64, (S + 63) / 64), n_it = (n_tiles + G - 1) / G;
+    const int n_tiles = min((q0 + QB + 63) / 64, (S + 63) / 64);
     const float scale = 1.0f / sqrtf((float)DH), sc2 = LOG2E * scale;
 
     bf16x8 qf[KS], dof[KS];
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __res
     }
     Dq += __shfl_xor(Dq, 32, 64);
     const size_t stat = ((size_t)b * h + head) * S + qc;
-    if (lh == 0 && q < S && grp == 0) Dbuf[stat] = Dq;
+    if (lh == 0 && q < S) Dbuf[stat] = Dq;
     const float nlse2 = -lse[stat] * LOG2E;
     f32x16 dqacc[CT];
 #pragma unroll
@@ -416,21 +416,20 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __res
       Stage<64, CPRK, NW>::issue(stage, wave, lane, ksrc(kv0));
       Stage<64, CPRK, NW>::issue(stage + K_CH, wave, lane, vsrc(kv0));
     };
-    issue_all(lds, min(grp, n_tiles - 1) * 64);
+    issue_all(lds, 0);
     stage_sync();
 
-    for (int it = 0; it < n_it; ++it) {
-      const int j = it * G + grp;
-      const u32x4* ktile = lds + (it & 1) * ST_CH;
+    for (int j = 0; j < n_tiles; ++j) {
+      const u32x4* ktile = lds + (j & 1) * ST_CH;
       const u32x4* vtile = ktile + K_CH;
-      u32x4* nxt = lds + ((it + 1) & 1) * ST_CH;
-      const int kv0 = j * 64, kvn = min(j + G, n_tiles - 1) * 64;
+      u32x4* nxt = lds + ((j + 1) & 1) * ST_CH;
+      const int kv0 = j * 64, kvn = min(j + 1, n_tiles - 1) * 64;
       issue_all(nxt, kvn);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {
         const int kg0 = kv0 + 32 * mt;
-        if (kg0 > qw0 + 31 || (SPLIT && j >= n_tiles)) continue;          // wave-uniform: every key of the group lies beyond every query of this wave
+        if (kg0 > qw0 + 31) continue;          // wave-uniform: every key of the group lies beyond every query of this wave
         f32x16 sacc, dpacc;
         zero16(sacc); zero16(dpacc);
         {
@@ -487,21 +486,6 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dq_kernel(const bf16_t* __res
       }
       __builtin_amdgcn_sched_barrier(0);
       stage_sync();
-    }
-    if constexpr (SPLIT) {          // (the loop's last barrier: the stages are free)
-      float* mg = reinterpret_cast<float*>(lds_all) + wave * 64 * 16 * CT + lane;
-      if (grp == 1) {
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) mg[(c * 16 + r) * 64] = dqacc[c][r];
-      }
-      __syncthreads();
-      if (grp == 1) return;
-#pragma unroll
-      for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dqacc[c][r] += mg[(c * 16 + r) * 64];
     }
     if (q < S) {
       unrotate_tile<DH>(dqacc, cosb, sinb, q, lh);          // dQ w.r.t. the un-rotated query (linear: commutes with the scale below)
@@ -730,9 +714,10 @@ static bool set_lds(K kern, int bytes) {
 
 // Pairing a heavy and a light block makes equal workgroups, which is what a full chip wants.  A grid whose last round is partly empty is as
 // slow as its longest workgroup, and single blocks, heaviest first, fill the gaps: paired only when the equal workgroups use at least 4 / 5 of
-// the slots of all their rounds (two forward workgroups of four waves, one dQ or dK/dV workgroup of eight waves per compute unit).  The order of a
-// row's sums does not depend on it.  us, paired / single, forward and backward: 8 x 1024, 12 heads of 64 (384, 192 and 384 paired workgroups on
-// 512, 256 and 256 slots) 33.4 + 109 / 27.6 + 100; 8 x 1000, 20 heads of 128 79.5 + 299 / 70.1 + 263; 8 x 512, 24 heads of 64 23.4 + 77 / 20.7 + 68.
+// the slots of all their rounds (two forward workgroups of four waves, one dK/dV workgroup of eight waves per compute unit).  The order of a
+// row's sums does not depend on it.  us, paired / single, forward, and backward with only its dK/dV kernel changed: 8 x 1024, 12 heads of 64 (384
+// paired workgroups on 512 and 256 slots) 33.4 + 98.5 / 27.6 + 83.8; 8 x 1000, 20 heads of 128 79.5 + 255 / 70.1 + 239; 8 x 512, 24 heads of 64 23.4 + 69.5 /
+// 20.7 + 60.1.
 static int full_rounds(long wgs, long slots) { return 5 * wgs >= 4 * slots * ((wgs + slots - 1) / slots); }
 
 template <int DH>
@@ -752,28 +737,24 @@ template <int DH>
 static int bwd_launch(hipStream_t st, const void* qkv, const void* o, const float* lse, const void* dO, void* dqkv, float* Dbuf,
                       int B, int S, int h, const float* cosb, const float* sinb) {
   constexpr int DQ_LDS = 2 * (2 * 64 * (DH / 8)) * 16;                                   // two stages of K rows + V rows
-  constexpr int SPLIT_LDS = 2 * DQ_LDS;                                                  // for each of the two groups of waves (the merge needs half of it)
   constexpr int DKV_LDS = (3 * (2 * 64 * (DH / 8)) + 2 * (2 * 4 * 2 * 64) + 3 * 32) * 16;          // three sets of Q rows + dO rows, two P mailboxes, three sets of statistics
-  static bool ok = set_lds(attn_bwd_dq_kernel<DH, false, true>, DQ_LDS) && set_lds(attn_bwd_dq_kernel<DH, false, false>, DQ_LDS) &&
-                   set_lds(attn_bwd_dq_kernel<DH, true, false>, SPLIT_LDS) && set_lds(attn_bwd_dkv_kernel<DH, true>, DKV_LDS) && set_lds(attn_bwd_dkv_kernel<DH, false>, DKV_LDS);
+  static bool ok = set_lds(attn_bwd_dq_kernel<DH, 4>, DQ_LDS) && (DH == 64 || set_lds(attn_bwd_dq_kernel<128, 8>, DQ_LDS)) &&
+                   set_lds(attn_bwd_dkv_kernel<DH, true>, DKV_LDS) && set_lds(attn_bwd_dkv_kernel<DH, false>, DKV_LDS);
   if (!ok) return 1;
   const int nb_kv = (S + 127) / 128, nb_dq = (S + 255) / 256;
   const long paired_dq = (long)B * h * ((nb_dq + 1) / 2), paired_kv = (long)B * h * ((nb_kv + 1) / 2);
   // the dQ kernel also writes D = rowsum(dO * O), which the dK/dV kernel then reads.
-  // Grids that leave compute units idle split the dQ blocks' KV tiles over two groups of waves; the line is where the single blocks no longer
-  // fit the chip in two rounds, moved up at head dim 64 for long rows, whose chain weighs more than another round's start-up.  us, whole backward,
-  // paired / split and single: 3 x 777, 12 x 64 68 / 41; 2 x 2048, 12 x 64 113 / 77; 1 x 2048, 16 x 128 174 / 116; 2 x 2048, 16 x 128 183 / 157; 8 x 300, 4 x 128
-  // 55 / 33; against it 8 x 512, 24 x 64 (768 blocks of at most 8 tiles) 76.9 / 79.7.  (The forward kernel is not split: its sums keep their order.)
-  const long single = (long)B * h * nb_kv;
-  if (nb_kv > 1 && paired_dq < 256 && (single <= 512 || (DH == 64 && single <= 768 && nb_kv >= 6)))
-    attn_bwd_dq_kernel<DH, true, false><<<dim3(B * h * nb_kv), 512, SPLIT_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h,
-                                                                                     B * h, nb_kv, cosb, sinb);
-  else {
-    const int pr = full_rounds(paired_dq, 256);
-    auto kern = pr ? attn_bwd_dq_kernel<DH, false, true> : attn_bwd_dq_kernel<DH, false, false>;
-    kern<<<dim3((unsigned)(pr ? paired_dq : (long)B * h * nb_dq)), 512, DQ_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h, B * h, nb_dq,
-                                                                                      cosb, sinb);
-  }
+  // Single blocks of 128 queries fill every grid best but some at head dim 128 with 1024 positions and more, where equal workgroups that
+  // fill the chip once, or three times and more, lose nothing to a last round and read K and V half as often.  us, paired 256 / single 128,
+  // whole backward: dh 64: 3 x 777, 12 heads 60 / 41; 8 x 1024, 12 heads 98.6 / 89.4; 8 x 2048, 16 heads 339 / 327; dh 128: 1 x 200, 8 heads 33 / 27; 8 x 129,
+  // 26 heads 35.2 / 34.9; 1 x 2048, 16 heads 162 / 121; 8 x 2048, 16 heads (512 paired) 596 / 578; against it 8 x 1024, 64 heads (1024 paired) 762 / 778; 16 x
+  // 2048, 16 heads (1024) 1199 / 1230; 2 x 4096, 16 heads (256) 484 / 491.
+  if (DH == 128 && S >= 1024 && full_rounds(paired_dq, 256) && (paired_dq <= 256 || paired_dq > 512))
+    attn_bwd_dq_kernel<128, 8><<<dim3((unsigned)paired_dq), 512, DQ_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h, B * h, nb_dq,
+                                                                               cosb, sinb);
+  else
+    attn_bwd_dq_kernel<DH, 4><<<dim3((unsigned)B * h * nb_kv), 256, DQ_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h, B * h, nb_kv,
+                                                                                  cosb, sinb);
   const int pair_kv = full_rounds(paired_kv, 256);
   auto kern = pair_kv ? attn_bwd_dkv_kernel<DH, true> : attn_bwd_dkv_kernel<DH, false>;
   kern<<<dim3((unsigned)(pair_kv ? paired_kv : (long)B * h * nb_kv)), 512, DKV_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h, B * h, nb_kv, cosb, sinb);
