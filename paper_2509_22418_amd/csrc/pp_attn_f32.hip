@@ -325,20 +325,27 @@ static int fwd_f32(hipStream_t st, const void* qkv, void* o, float* lse, int B, 
            else if (dh == 64) { constexpr int DH = 64; CALL; } else { constexpr int DH = 128; CALL; } }                                     \
   } while (0)
 
-// A few hundred rows of at most 32 positions are one short pass for the vector kernels (a workgroup per row) and a chain of three dependent
-// phases on few workgroups here (us, vector kernels / these, forward and backward: 4 x 32 tokens, 4 heads of 16: 5.3 + 12.4 / 8.4 + 13.1; 4 heads of 64:
-// 8.5 + 24.2 / 10.3 + 24.3; but 16 x 32 tokens, 16 heads of 32: 36 + 131 / 8.9 + 17.1; 4 x 64 tokens, 4 heads of 64: 13.2 + 62 / 11.1 + 26).
-static bool few_short_rows(int B, int S, int h) { return S <= 32 && (long)B * h * S <= 1024; }
+// Few rows, short rows: the vector kernels run a workgroup per row, all at once up to about 3000 of them, and then last as long as one row;
+// here a workgroup of 32 rows is a chain of three dependent phases.  What pays is pairs x S^2 (pairs = B h), and for the backward, whose
+// vector chain is longer, also the length alone.  The lines below are where both took the same time (pairs 1 .. 128, S 1 .. 1150; fp32, us, vector / these):
+//   forward   dh 16: 16 x 33 5.4 / 8.4, 16 x 80 8.0 / 9.8, 32 x 64 11.0 / 8.8, 4 x 200 13.8 / 14.4, 4 x 256 18.5 / 15.7
+//             dh 32: 64 x 33 7.7 / 8.8, 96 x 32 14.8 / 8.7, 8 x 128 17.2 / 11.8     dh 64: 16 x 48 9.5 / 10.4, 16 x 64 12.7 / 11.2, 64 x 32 11.9 / 10.3
+//   backward  dh 64: 1 x 48 22.7 / 24.7, 1 x 64 28.3 / 25.1, 32 x 32 27.2 / 24.6     dh 128: 4 x 64 43.5 / 45.4, 1 x 128 61.3 / 53.7, 8 x 80 69.2 / 48.1
+static bool fwd_pays(long pairs, int S, int dh) {
+  if (dh == 32 && S >= 32 && pairs * S >= 3072) return true;
+  return pairs * S * S >= (dh >= 64 ? 1 << 16 : dh == 16 && pairs < 8 ? 1 << 18 : 1 << 17);
+}
+static bool bwd_pays(long pairs, int S, int dh) { return dh == 128 ? S >= 128 || pairs * S * S >= 40000 : S >= 64 || pairs * S * S >= 1 << 15; }
 // The scores of 32 queries against the whole sequence sit in LDS: up to 1152 positions; longer ones return 1.
 int k_attn_fwd_f32(hipStream_t st, int dtype, const void* qkv, void* o, float* lse, int B, int S, int h, int dh) {
-  if (!shapes_ok(dtype, qkv, o, S, h, dh) || few_short_rows(B, S, h)) return 1;
+  if (!shapes_ok(dtype, qkv, o, S, h, dh) || !fwd_pays((long)B * h, S, dh)) return 1;
   const int pitch = ((S + 31) & ~31) + 1;
   int rc = 1;
   PP_F32_ATTN(dtype, dh, (rc = fwd_f32<DH, T>(st, qkv, o, lse, B, S, h, pitch)));
   return rc;
 }
 int k_attn_bwd_f32(hipStream_t st, int dtype, const void* qkv, const void* o, const float* lse, const void* dO, void* dqkv, float* Dbuf, int B, int S, int h, int dh) {
-  if (!shapes_ok(dtype, qkv, dO, S, h, dh) || few_short_rows(B, S, h)) return 1;
+  if (!shapes_ok(dtype, qkv, dO, S, h, dh) || !bwd_pays((long)B * h, S, dh)) return 1;
   k_attn_D(st, dtype, o, dO, Dbuf, B, S, h, dh);
   const unsigned grid = (unsigned)B * h * ((S + 31) / 32);
   PP_F32_ATTN(dtype, dh, (attn_bwd_dq_f32_kernel<DH, T><<<grid, 256, 0, st>>>((const T*)qkv, lse, Dbuf, (const T*)dO, (T*)dqkv, S, h, B * h)));

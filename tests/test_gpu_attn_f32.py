@@ -53,3 +53,28 @@ def test_values_that_are_not_finite_stay_behind_the_mask(value):
     for a, b in zip(got, ref):
         assert torch.equal(torch.isnan(a), torch.isnan(b))
         assert torch.equal(torch.nan_to_num(a, nan=7.0), torch.nan_to_num(b, nan=7.0))
+
+
+# (B, S, h, dh, bf16): short rows and few rows, where a workgroup per row is the faster split
+@pytest.mark.parametrize("B,S,h,dh,dtype", [(4, 33, 4, 16, "f32"), (1, 48, 1, 16, "f32"), (8, 16, 12, 16, "f32"), (1, 33, 1, 128, "f32"), (1, 40, 2, 16, "bf16"), (1, 100, 4, 32, "f32")])
+def test_few_short_rows_are_not_slower_than_on_the_plain_kernels(B, S, h, dh, dtype):
+    print(f"case attention few rows B={B} S={S} h={h} dh={dh} {dtype}", flush=True)
+    td, dt = (torch.bfloat16, pp.PP_BF16) if dtype == "bf16" else (torch.float32, pp.PP_F32)
+    qkv, dO = torch.randn((B * S, 3 * h * dh), device="cuda").to(td), torch.randn((B * S, h * dh), device="cuda").to(td)
+    o, dqkv = torch.empty_like(dO), torch.empty_like(qkv)
+    lse, rows = (torch.empty(B * h * S, device="cuda") for _ in range(2))
+    st = torch.cuda.current_stream().cuda_stream
+    fwd = lambda path: pp.pp_op_attention_fwd(st, dt, qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), None, B, S, h, dh, path)  # noqa: E731
+    bwd = lambda path: pp.pp_op_attention_bwd(st, dt, qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), dO.data_ptr(), dqkv.data_ptr(), rows.data_ptr(), None, B, S, h, dh, path)  # noqa: E731
+    for call in (fwd, bwd):
+        best = [float("inf")] * 2
+        for _ in range(8):
+            for path in (0, 1):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                for _ in range(50):
+                    call(path)
+                b.record()
+                torch.cuda.synchronize()
+                best[path] = min(best[path], a.elapsed_time(b))
+        assert best[0] <= 1.2 * best[1], best
