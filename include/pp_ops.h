@@ -54,8 +54,8 @@ int pp_op_gemm_nt_splitk_static(void* hip_stream, int dtype, const void* A_dev, 
  * factorisation of Section 2.1).  qkv_dev: [B*S x 3*h*dh], columns q | k | v, head j at columns j*dh of each part
  * (q and k already rotated).  o_dev: [B*S x h*dh].  lse_dev: float [B*h*S], log-sum-exp of the scaled scores.
  * scratch_dev: not used (the matrix-core kernels read q, k, v as stored); kept in the signature, may be NULL.
- * path: 0 = automatic (bf16 MFMA kernels for bf16 with dh 64 or 128; otherwise the fp32-multiply MFMA kernels for dh 16, 32, 64, 128 --
- * forward up to 1152 positions --, which return the plain kernels' bits), 1 = plain kernels. */
+ * path: 0 = automatic (bf16 MFMA kernels for bf16 with dh 64 or 128; otherwise, where there are rows enough for them, the fp32-multiply
+ * MFMA kernels for dh 16, 32, 64, 128 -- forward up to 1184 positions --, which return the plain kernels' bits), 1 = plain kernels. */
 int pp_op_attention_fwd(void* hip_stream, int dtype, const void* qkv_dev, void* o_dev, float* lse_dev, void* scratch_dev,
                         int B, int S, int h, int dh, int path);
 

@@ -1,5 +1,5 @@
-// Causal attention in fp32 multiplies on the matrix cores, for fp32 models and for bf16 head dims that the bf16 kernels do not take:
-// head dims 16, 32, 64 and 128, any sequence length (forward: up to the scores of 32 queries in LDS, see the launcher).
+// Causal attention in fp32 multiplies on the matrix cores, for fp32 models and for what the bf16 kernels do not take (head dims 16 and 32,
+// tensors on 8-byte but not 16-byte boundaries): head dims 16, 32, 64 and 128, any sequence length (forward: up to the scores of 32 queries in LDS, MAX_S).
 //
 // Same bits as the plain kernels.  v_mfma_f32_32x32x2 / 16x16x4 add their products one after the other with one rounding each,
 // so an accumulator fed in index order is the plain kernel's fmaf chain: scores run over the head dim, P V / dS K over the keys and
@@ -308,12 +308,13 @@ static bool shapes_ok(int dtype, const void* a, const void* b, int S, int h, int
   const uintptr_t al = dtype == 0 ? 15 : 7;          // rows are read four elements at a time
   return S >= 1 && h >= 1 && (dh == 16 || dh == 32 || dh == 64 || dh == 128) && (((uintptr_t)a | (uintptr_t)b) & al) == 0;
 }
+constexpr int MAX_S = 1184;                               // positions, a multiple of 32 (rows are padded to one)
+constexpr int MAX_LDS = (32 * (MAX_S + 1) + 32) * 4;      // forward: 32 rows of scores and their sums, 148 KB of the compute unit's 160
 template <int DH, class T>
 static int fwd_f32(hipStream_t st, const void* qkv, void* o, float* lse, int B, int S, int h, int pitch) {
-  constexpr int MAX_LDS = 150 * 1024;
   static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_fwd_f32_kernel<DH, T>), hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS) == hipSuccess;
   const int bytes = (32 * pitch + 32) * 4;
-  if (!ok || bytes > MAX_LDS) return 1;
+  if (!ok) return 1;
   attn_fwd_f32_kernel<DH, T><<<dim3((unsigned)B * h * ((S + 31) / 32)), 256, bytes, st>>>((const T*)qkv, (T*)o, lse, S, h, B * h, pitch);
   return 0;
 }
@@ -336,9 +337,9 @@ static bool fwd_pays(long pairs, int S, int dh) {
   return pairs * S * S >= (dh >= 64 ? 1 << 16 : dh == 16 && pairs < 8 ? 1 << 18 : 1 << 17);
 }
 static bool bwd_pays(long pairs, int S, int dh) { return dh == 128 ? S >= 128 || pairs * S * S >= 40000 : S >= 64 || pairs * S * S >= 1 << 15; }
-// The scores of 32 queries against the whole sequence sit in LDS: up to 1152 positions; longer ones return 1.
+// The scores of 32 queries against the whole sequence sit in LDS: sequences of more than MAX_S positions return 1.
 int k_attn_fwd_f32(hipStream_t st, int dtype, const void* qkv, void* o, float* lse, int B, int S, int h, int dh) {
-  if (!shapes_ok(dtype, qkv, o, S, h, dh) || !fwd_pays((long)B * h, S, dh)) return 1;
+  if (S > MAX_S || !shapes_ok(dtype, qkv, o, S, h, dh) || !fwd_pays((long)B * h, S, dh)) return 1;
   const int pitch = ((S + 31) & ~31) + 1;
   int rc = 1;
   PP_F32_ATTN(dtype, dh, (rc = fwd_f32<DH, T>(st, qkv, o, lse, B, S, h, pitch)));
