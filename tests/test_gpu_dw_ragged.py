@@ -45,7 +45,7 @@ def test_ragged_token_counts_match_the_plain_kernels(B, S, mname):
 
 @pytest.mark.parametrize("M,N,splits", [(1024, 2048, 8), (1024, 2048, 4), (1160, 2056, 16), (1160, 2056, 6)])
 def test_more_ranges_than_fill_the_gpu_are_joined(M, N, splits):
-    """128 and 170 tiles: four and eight (but not six) ranges are run as fewer.  fp32 sums of at most K products and `splits` partial
+    """128 tiles: eight ranges are run as four, four as four.  170 tiles: sixteen are run as four, six as six.  fp32 sums of at most K products and `splits` partial
     sums: (K + splits) half-ulp roundings of sum |a b| bound the error, and no partial is left out or added twice."""
     K = 64 * splits * 2
     g = torch.Generator(device="cuda").manual_seed(9)
@@ -58,3 +58,20 @@ def test_more_ranges_than_fill_the_gpu_are_joined(M, N, splits):
     ref = A.double().T.contiguous() @ B.double()
     bound = A.double().abs().T.contiguous() @ B.double().abs()
     assert bool(((C.double() - ref).abs() <= (K + splits) * 2.0 ** -24 * bound).all())
+
+
+@pytest.mark.parametrize("splits", [2, 4])
+def test_joined_ranges_are_summed_apart(splits):
+    """512 tiles: all ranges joined to one, which writes C itself.  The first range of 128 rows sums to 2^30 (spacing 128), each later one to 128
+    by sixteens: added one by one they would be lost, as sums of their own they are exact.  Rows of C are longer than N."""
+    M, N, K, ldc = 2048, 4096, 128 * splits, 4104
+    col = torch.ones(K, 1, device="cuda")
+    col[:128] = 0.0
+    col[5] = 2.0 ** 15
+    A, B = (col.expand(K, n).bfloat16().contiguous() for n in (M, N))
+    C = torch.full((M, ldc), 7.0, device="cuda")
+    scratch = torch.empty((M * N * splits,), device="cuda")
+    pp.pp_op_gemm_tn(torch.cuda.current_stream().cuda_stream, A.data_ptr(), M, M, 0, B.data_ptr(), N, C.data_ptr(), ldc, M, N, K, splits, scratch.data_ptr())
+    torch.cuda.synchronize()
+    assert bool((C[:, :N] == 2.0 ** 30 + 128.0 * (splits - 1)).all())
+    assert bool((C[:, N:] == 7.0).all())
