@@ -605,7 +605,7 @@ static void gemm_dw_tn(pp_model* m, const void* A, int lda, int m_blk, long a_bl
     }
     timer.cancel();
   }
-  if (m->cfg.dtype == PP_F32 && !m->force_plain) {          // fp32: token-major operands too; same K ranges and order of sums as below
+  if (m->cfg.dtype == PP_F32 && !m->force_plain && m->dw_tn) {          // fp32: token-major operands too; same K ranges and order of sums as below
     const int splits = dw_splits(m, M, N, K);
     float* partial = (float*)(m->wsp + m->ws.partial);
     GemmTimer timer(m, 2.0 * M * N * K);

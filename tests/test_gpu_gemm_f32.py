@@ -78,3 +78,22 @@ def test_f32_step_weight_gradients_match_the_plain_kernels(B, S, over, mname):
         m.close()
     assert loss[0] == loss[1]
     assert np.array_equal(g[0], g[1])
+
+
+def test_f32_weight_gradients_through_transposed_copies_have_the_same_bits():
+    """Option dw_tn = 0 sends an fp32 model's weight gradients through transposed copies (which appear in the workspace: two runs alike leave it
+    alike) with the same ranges and order of sums."""
+    cfg = gen.make_config("tiny", batch=2, seq=257)
+    m = pp.LocalStepModel(cfg, gen.all_mask(cfg))
+    m.load_weights(gen.make_weights(cfg, seed=5))
+    m.set_mask()
+    tok = m.upload_tokens(*gen.make_tokens(cfg, seed=5))
+    g, ws = [], []
+    for dw_tn in (1, 1, 0):
+        m.set_option("dw_tn", dw_tn)
+        m.step(*tok, None)
+        g.append(m.get_state("g"))
+        ws.append(m.ws.clone())
+    m.close()
+    assert np.array_equal(g[0], g[1]) and np.array_equal(g[0], g[2])
+    assert torch.equal(ws[0], ws[1]) and not torch.equal(ws[0], ws[2])
