@@ -30,8 +30,8 @@ int pp_op_gemm_nt(void* hip_stream, int dtype, const void* A_dev, int lda, const
  * (m / m_blk) * a_blk_stride + m % m_blk of A (m_blk = M, a_blk_stride = 0 for one contiguous column range).
  * splits > 1 (scratch_dev of M*N*splits floats): K is cut into at most `splits` equal ranges (fewer when those fill the GPU)
  * whose partial products are summed in fixed order.  MFMA kernel only (bf16): needs M, N, lda, ldb, m_blk, a_blk_stride multiples of 8, K a multiple of
- * 64*splits, and m_blk a multiple of 128 when M > m_blk; other shapes return PP_EINVAL (pp_local_step then goes through
- * transposed copies and pp_op_gemm_nt's kernels instead). */
+ * 64*splits, and m_blk a multiple of 128 when M > m_blk; other shapes return PP_EINVAL (pp_local_step itself runs the kernel for any token
+ * count and column blocks of any multiple of 8, in ranges of its own, and goes through transposed copies for the rest). */
 int pp_op_gemm_tn(void* hip_stream, const void* A_dev, int lda, int m_blk, int64_t a_blk_stride, const void* B_dev, int ldb, float* C_dev,
                   int ldc, int M, int N, int K, int splits, float* scratch_dev);
 

@@ -580,14 +580,16 @@ static void gemm_dw(pp_model* m, const void* At, const void* Bt, float* G, int M
 
 // Weight gradient from token-major operands: G[M x N] (fp32, ld N) = A^T B, A [K x M'] (lda) and B [K x N] (ldb) as the
 // forward / backward passes left them, K = tokens; column m of the product is column (m / m_blk) * a_blk_stride + m % m_blk
-// of A.  The MFMA kernel gathers its operands with LDS transpose reads; shapes it does not take (and fp32 storage) go
-// through transposed copies and gemm_dw.
+// of A.  The bf16 MFMA kernel gathers its operands with LDS transpose reads, fp32 storage has a token-major kernel too; shapes they do
+// not take go through transposed copies and gemm_dw.
 static void gemm_dw_tn(pp_model* m, const void* A, int lda, int m_blk, long a_blk_stride, const void* B, int ldb, float* G, int M, int N, int K) {
   const size_t es = esize(m->cfg);
-  // (measured at K = 16384: up to 256 tiles of 128 x 128 -- the row-block slices, which need split-K anyway, and d x d --
-  // the transpose-read kernel beats transposing both operands and running the 256 x 256-tile NT kernel; above that the
-  // NT kernel's higher rate outweighs the two extra passes.  A token count that is not a multiple of 64 always comes here: the
-  // transposed copies would have rows the NT kernel does not take.)
+  // Up to 256 tiles of 128 x 128 -- the row-block slices, which need split-K anyway, and d x d -- the transpose-read kernel beats transposing
+  // both operands and running the 256 x 256-tile NT kernel; far above that the NT kernel's higher rate outweighs the two extra passes.  The line
+  // is from a kernel that waited for all its loads at every transpose read; the present one (us, token-major / copies + NT): 2048 x 2048 over 16384
+  // rows (256 tiles) 206 / 301, 3072 x 2048 over 8192 (384) 125 / 164, 4096 x 2048 over 16384 (512) 286 / 341, 6144 x 2048 (768) 472 / 404, 32000 x 2048
+  // over 8192 (4000) 1154 / 1008, 32000 x 768 over 8192 (1500) 441 / 574.  Same bits either way.  A token count that is not a multiple of 64 always
+  // comes here: the transposed copies would have rows the NT kernel does not take.
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
   if (m->cfg.dtype == PP_BF16 && !m->force_plain && m->dw_tn && (tiles <= 256 || K % 64)) {
     const size_t out_bytes = (size_t)M * N * 4;

@@ -1,4 +1,4 @@
-// fp32-multiply MFMA GEMM for gfx950 (fp32 operands, fp32 accumulate), any shape and alignment:
+// fp32-multiply MFMA GEMM for gfx950 (fp32 operands, fp32 accumulate), any M, N, K and alignment:
 //   NT:  C[M x N] = A[M x K] B[N x K]^T (+ R)      both operands K-contiguous (projections, input gradients)
 //   TN:  C[M x N] = A^T B, A [K x M'], B [K x N]    both operands token-major (weight gradients; no transposed copies)
 // It carries every contraction of an fp32 model, and the bf16 contractions whose K or alignment the bf16 MFMA kernels do
@@ -16,7 +16,9 @@
 //   * 32 x 32 tile, four waves of 16 x 16 (16x16x4 MFMAs: 8 cycles per k), K steps of 64, otherwise: four times the
 //     workgroups and a quarter of the serial chain, which is what a launch of few tiles lasts as long as.
 // Staging goes through registers (two sets, loads run two K steps ahead) by buffer loads: a piece past the last row, column
-// or k is given an offset outside the buffer and reads as zero without a branch, so no shape is refused.  An NT panel row is cut into groups of 8 (16) k; the 16-byte chunk i of a group holds the k
+// or k is given an offset outside the buffer and reads as zero without a branch, so edges and remainders need no case of their own.
+// Not taken: rows so long that a tile's offsets pass 31 bits (offsets_fit: about 8.3 M elements), and TN column blocks that are not
+// multiples of 4.  An NT panel row is cut into groups of 8 (16) k; the 16-byte chunk i of a group holds the k
 // that lane group i needs (k = i mod 2, resp. mod 4), so one 16-byte read feeds four MFMAs.  Chunks are permuted by row so that
 // neither the fragment reads (16 rows, one chunk) nor the writes conflict on the 64 banks.  TN panels are stored [k][m] as they lie
 // in memory, with bit 5 (bit 4) of m flipped for every second k (pair of k), and are read 4 bytes per lane.
@@ -25,7 +27,6 @@
 
 namespace pp {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr uint32_t OOB = 0x80000000u;          // past every buffer below: reads as zero
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_of(const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffff, 0x00020000); }
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const T* __restrict_
 
   // ---- staging: piece i of this thread is 4 elements of one panel row (NT: 4 k of a row; TN: 4 columns of one k)
   // Offsets are relative to the tile's first row (NT; the step enters as a uniform offset) or to the step's first k (TN; the base
-  // pointer moves), so that they fit 31 bits for any matrix.
+  // pointer moves), so that they fit 31 bits whatever M and N are; the launchers check the rows' lengths (offsets_fit).
   uint32_t oa[NV], ob[NV];
   int va[NV], vb[NV], kk[NV], row[NV];          // elements that exist (TN: columns; NT: 4 or 0).  kk = k of the piece within a step
 #pragma unroll
@@ -228,7 +229,7 @@ static void launch_f32(hipStream_t st, const void* A, const void* B, void* C, co
   else launch_f32<T, TO, TN, false>(st, A, B, C, R, g, splits);
 }
 
-// Offsets within a tile's 64 rows (NT: plus all of K) are 32-bit: rows of 8 M elements and more stay on the vector kernel.
+// Offsets within a tile's 64 rows (NT: plus all of K) are 31-bit: longer rows stay on the vector kernel (TN: are refused).
 static bool offsets_fit(int lda, int ldb, int K) { return (64ull * (size_t)(lda > ldb ? lda : ldb) + (size_t)K) * 4 < 0x7f000000ull; }
 // rows of groups of four elements that can be read at once
 static bool vec4_ok(int dtype, const void* p, int ld) { return ld % 4 == 0 && ((uintptr_t)p & (dtype == 0 ? 15 : 7)) == 0; }

@@ -13,8 +13,8 @@
 // Tiling: 128 x 128 output tile per workgroup of 256 threads (4 waves, 2 x 2, each 64 x 64 = 2 x 2 blocks of
 // v_mfma_f32_32x32x16_bf16, 64 accumulator registers); K advances in steps of 64 rows; two LDS stages of 16 KB per
 // operand (64 KB per workgroup, two workgroups per compute unit), the next step's tiles in flight while the current one
-// is multiplied, one barrier per step.  (A ring of four 32-row stages with three steps in flight was measured slower on
-// every shape: the cost per step is the barrier and the first fragment reads behind it, not the loads.)  Tiles are filled
+// is multiplied, one barrier per step.  (A ring of four 32-row stages was slower on every shape when each
+// transpose read still waited for all loads in flight, see read_frags; it has not been timed since.)  Tiles are filled
 // by direct-to-LDS loads (one wave load = 4 rows); the 16-byte chunk c of row r is stored at chunk c ^ ((r & 3) << 2), applied on the source side, so
 // that the 4 rows x 2 x 32 bytes touched by one phase of a transpose read fall into 8 different 32-byte bank groups.
 // Few output tiles and a long K: the K range is split over blockIdx.y; partial products are summed in fixed order by
@@ -29,7 +29,6 @@ namespace pp {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int TN_BM = 128, TN_BN = 128, TN_BK = 64;
 constexpr int TN_OPERAND_BYTES = TN_BK * 256;                 // 64 rows of 128 elements

@@ -53,12 +53,13 @@ void k_gemm_nt_plain_splitk(hipStream_t st, int dtype, const void* A, int lda, c
                             int M, int N, int K, int splits);
 void k_splitk_reduce(hipStream_t st, const float* partial, float* C, int ldc, int M, int N, int splits);
 
-// fp32-multiply MFMA GEMMs, any shape and alignment, fp32 or bf16 storage (pp_gemm_f32.hip).  K % splits == 0; splits > 1:
+// fp32-multiply MFMA GEMMs, any M, N, K and alignment, fp32 or bf16 storage (pp_gemm_f32.hip; rows of about 8.3 M elements and more go to the
+// vector kernel).  K % splits == 0; splits > 1:
 // `partial` receives [splits][M][N] floats and C is not written (k_splitk_reduce sums them).
 void k_gemm_nt_f32(hipStream_t st, int dtype, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, int epi, const void* R,
                    int out_f32, int splits, float* partial);
 // C[M x N] fp32 = A^T B, A's columns in blocks as in k_gemm_tn_mfma; returns 1 (nothing launched) if M > m_blk and a group of four
-// columns could straddle two blocks
+// columns could straddle two blocks, or if rows are too long
 int k_gemm_tn_f32(hipStream_t st, const float* A, int lda, int m_blk, long a_blk_stride, const float* B, int ldb, float* C, int ldc, int M, int N, int K,
                   int splits, float* partial);
 

@@ -56,7 +56,15 @@ def test_gemm_nt_f32_matches_fp64(M, N, K, pad, res, splits, dtype):
     assert bool(((C.double() - ref).abs() <= tol).all())
 
 
-@pytest.mark.parametrize("B,S,over", [(1, 1, {}), (3, 19, dict(d_model=72, n_heads=3, d_ff=200, vocab=264)), (2, 150, dict(d_model=96, n_heads=6, d_ff=136, vocab=520))])
+STEPS = [
+    (1, 1, {}), (3, 19, dict(d_model=72, n_heads=3, d_ff=200, vocab=264)), (2, 150, dict(d_model=96, n_heads=6, d_ff=136, vocab=520)),
+    (2, 512, {}),                                                             # 1024 tokens: four K ranges, summed in order
+    (2, 257, dict(n_layers=1, d_model=264, n_heads=3, vocab=8200)),           # lm_head: 645 tiles of 64 x 64; two K ranges of 257 tokens elsewhere
+    (1, 37, dict(d_model=48, n_heads=8, d_ff=72, vocab=104)),                 # head dim 6: column blocks of 12 at an offset of 6, no vector loads
+]
+
+
+@pytest.mark.parametrize("B,S,over", STEPS)
 @pytest.mark.parametrize("mname", ["all", "heads"])
 def test_f32_step_weight_gradients_match_the_plain_kernels(B, S, over, mname):
     """Token-major weight gradients (column blocks, ragged token counts) and projections of an fp32 model add in the order of the
