@@ -1,5 +1,7 @@
 """Weight gradients over token counts that are not a multiple of the token-major kernel's K step, and column blocks that are not
 whole tiles: a bf16 step against the same step on the plain kernels."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -75,3 +77,27 @@ def test_joined_ranges_are_summed_apart(splits):
     torch.cuda.synchronize()
     assert bool((C[:, :N] == 2.0 ** 30 + 128.0 * (splits - 1)).all())
     assert bool((C[:, N:] == 7.0).all())
+
+
+@pytest.mark.parametrize("K", [1, 63, 65, 130, 200])
+def test_infinities_in_the_last_row_reach_no_padding(K):
+    """The last K step of a ragged count is filled up with copies of the last row and then with zeros.  An infinity in that row gives
+    infinities of the right sign where its own products do, and no NaN: neither panel is zeroed without the other.  (The kernel's C++
+    entry: the C one takes whole steps only.)"""
+    print(f"case dw last row K={K}", flush=True)
+    M, N = 136, 72
+    tn = ctypes.CDLL(pp.lib_path())["_ZN2pp14k_gemm_tn_mfmaEP12ihipStream_tPKviilS3_iPfiiiiiS4_i"]
+    P, I = ctypes.c_void_p, ctypes.c_int
+    tn.argtypes = [P, P, I, I, ctypes.c_long, P, I, P, I, I, I, I, I, P, I]
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A, B = (torch.randn((K, n), device="cuda", generator=g).bfloat16() for n in (M, N))
+    A[-1, 3] = float("inf")
+    B[-1, 70] = float("-inf")
+    C = torch.zeros((M, N), device="cuda")
+    assert tn(torch.cuda.current_stream().cuda_stream, A.data_ptr(), M, M, 0, B.data_ptr(), N, C.data_ptr(), N, M, N, K, (K + 63) // 64 * 64, None, 1 << 30) == 0
+    torch.cuda.synchronize()
+    ref, bound = A.double().T.contiguous() @ B.double(), A.double().abs().T.contiguous() @ B.double().abs()
+    fin = torch.isfinite(ref)
+    assert int((~fin).sum()) == M + N - 1 and not bool(torch.isnan(ref).any())
+    assert torch.equal(C.double()[~fin], ref[~fin])
+    assert bool(((C.double() - ref).abs()[fin] <= K * 2.0 ** -24 * bound[fin]).all())
