@@ -12,6 +12,8 @@
 #include "pp_kernels.h"
 #include "pp_dev.h"
 
+#include <type_traits>
+
 namespace pp {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -121,43 +123,47 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_ring_kernel(const bf16_t
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
         *reinterpret_cast<float4*>(patch + (i * 16 + l16) * PITCH + j * 64 + lq * 16) = make_float4(acc[2 * p + i][j][0], acc[2 * p + i][j][1], acc[2 * p + i][j][2], acc[2 * p + i][j][3]);
+    auto store = [&](auto V) {          // V consecutive columns exist as a whole and are aligned
+      constexpr int VEC = decltype(V)::value;
 #pragma unroll
-    for (int it = 0; it < NP; ++it) {
-      const int idx = it * 64 + lane, row = idx / PR, c = idx % PR;
-      const float4 v0 = *reinterpret_cast<const float4*>(patch + row * PITCH + c * 32);
-      const float4 v1 = *reinterpret_cast<const float4*>(patch + row * PITCH + c * 32 + 16);
-      const int grow = m0 + wm * TM + p * 32 + row, gcol = n0 + wn * TN + c * 8;
-      if (grow >= M || gcol >= N) continue;
-      float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-      const size_t off = (size_t)grow * ldc + gcol;
-      if (vec == 8) {          // 16-byte pieces exist as a whole and are aligned
-        if constexpr (EPI == EPI_ADD_RES) {
-          float r[8];
-          load8(R + off, r);
+      for (int it = 0; it < NP; ++it) {
+        const int idx = it * 64 + lane, row = idx / PR, c = idx % PR;
+        const float4 v0 = *reinterpret_cast<const float4*>(patch + row * PITCH + c * 32);
+        const float4 v1 = *reinterpret_cast<const float4*>(patch + row * PITCH + c * 32 + 16);
+        const int grow = m0 + wm * TM + p * 32 + row, gcol = n0 + wn * TN + c * 8;
+        if (grow >= M || gcol >= N) continue;
+        float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        const size_t off = (size_t)grow * ldc + gcol;
+        if constexpr (VEC == 8) {
+          if constexpr (EPI == EPI_ADD_RES) {
+            float r[8];
+            load8(R + off, r);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] += r[e];
-        }
-        store8(C + off, v);
-      } else if (vec == 4) {          // 8-byte pieces do
+            for (int e = 0; e < 8; ++e) v[e] += r[e];
+          }
+          store8(C + off, v);
+        } else {
 #pragma unroll
-        for (int e = 0; e < 8; e += 4)
-          if (gcol + e < N) {
-            if constexpr (EPI == EPI_ADD_RES) {
-              const uint2 r = *reinterpret_cast<const uint2*>(R + off + e);
-              v[e] += __uint_as_float(r.x << 16); v[e + 1] += __uint_as_float(r.x & 0xffff0000u);
-              v[e + 2] += __uint_as_float(r.y << 16); v[e + 3] += __uint_as_float(r.y & 0xffff0000u);
+          for (int e = 0; e < 8; e += VEC) {
+            if (gcol + e >= N) continue;
+            if constexpr (VEC == 4) {
+              if constexpr (EPI == EPI_ADD_RES) {
+                const uint2 r = *reinterpret_cast<const uint2*>(R + off + e);
+                v[e] += __uint_as_float(r.x << 16); v[e + 1] += __uint_as_float(r.x & 0xffff0000u);
+                v[e + 2] += __uint_as_float(r.y << 16); v[e + 3] += __uint_as_float(r.y & 0xffff0000u);
+              }
+              *reinterpret_cast<uint2*>(C + off + e) = make_uint2(f32x2_to_bf16x2(v[e], v[e + 1]), f32x2_to_bf16x2(v[e + 2], v[e + 3]));
+            } else {
+              if constexpr (EPI == EPI_ADD_RES) v[e] += to_f32(R[off + e]);
+              C[off + e] = from_f32<bf16_t>(v[e]);
             }
-            *reinterpret_cast<uint2*>(C + off + e) = make_uint2(f32x2_to_bf16x2(v[e], v[e + 1]), f32x2_to_bf16x2(v[e + 2], v[e + 3]));
           }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (gcol + e < N) {
-            if constexpr (EPI == EPI_ADD_RES) v[e] += to_f32(R[off + e]);
-            C[off + e] = from_f32<bf16_t>(v[e]);
-          }
+        }
       }
-    }
+    };
+    if (vec == 8) store(std::integral_constant<int, 8>{});
+    else if (vec == 4) store(std::integral_constant<int, 4>{});
+    else store(std::integral_constant<int, 1>{});
   }
 }
 
