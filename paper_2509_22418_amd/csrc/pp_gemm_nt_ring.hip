@@ -7,8 +7,10 @@
 // registers at the stage's one barrier, which therefore also frees its slot: stage s + NS is requested right behind it, so NS - 1 stages are
 // in flight while one is multiplied.  v_mfma_f32_16x16x32_bf16 with the B panel as row operand; the accumulators are turned
 // around through LDS into 16-byte row pieces, the residual is added in fp32 and the sum rounded once.
-// What bounds it: the feed.  A K step of a BM x BN tile is (BM + BN) * 128 bytes to load and BM * BN / 32 cycles of matrix pipe: 64 B per clock
-// and compute unit (all that a unit's load path moves) at 128 x 128, 53 at 128 x 192; the main loops reach 25 to 40.
+// What bounds it: a K step of a BM x BN tile is (BM + BN) * 128 bytes to load and BM * BN / 32 cycles of matrix pipe: 64 B per clock and
+// compute unit (all that a unit's load path moves) at 128 x 128, 53 at 128 x 192.  Over whole launches (profiles/op_kernels_pmc.txt) the four larger
+// tiles load 16 to 19 B per clock with the matrix pipe busy 0.28 to 0.46 and the waves waiting 0.31 to 0.40 of their cycles: latency behind the barriers,
+// and a fifth to a third of a one-round launch in which units start up or drain.
 #include "pp_kernels.h"
 #include "pp_dev.h"
 
