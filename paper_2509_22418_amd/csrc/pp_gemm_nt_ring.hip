@@ -3,17 +3,17 @@
 // The 256 x 256-tile kernel (one workgroup per compute unit, 160 KB of LDS) needs well over 256 tiles to fill the chip; the
 // 125M-shape decoder (d_model 768, 8192 tokens) has projections with 96.  One kernel template cuts the output into smaller tiles:
 // panels of BM and BN rows x 64 K-elements go straight to LDS (global_load_lds, rows of 128 bytes, chunk c of row r at
-// c ^ ((r >> 1) & 7): conflict-free fragment reads), NS such stages form a ring.  All of a tile's fragments of a stage are in
-// registers at the stage's one barrier, which therefore also frees its slot: stage s + NS is requested right behind it, so NS - 1 stages are
-// in flight while one is multiplied.  v_mfma_f32_16x16x32_bf16 with the B panel as row operand; the accumulators are turned
+// c ^ ((r >> 1) & 7): conflict-free fragment reads), NS such stages form a ring.  A stage's slot is filled again (with stage s + NS) as soon as its last fragments
+// are in registers.  v_mfma_f32_16x16x32_bf16 with the B panel as row operand; the accumulators are turned
 // around through LDS into 16-byte row pieces, the residual is added in fp32 and the sum rounded once.
 // What bounds it: a K step of a BM x BN tile is (BM + BN) * 128 bytes to load and BM * BN / 32 cycles of matrix pipe: 64 B per clock and
-// compute unit (all that a unit's load path moves) at 128 x 128, 53 at 128 x 192.  Over whole launches (profiles/op_kernels_pmc.txt) the four larger
-// tiles load 16 to 19 B per clock with the matrix pipe busy 0.28 to 0.46 and the waves waiting 0.31 to 0.40 of their cycles: latency behind the barriers,
-// and a fifth to a third of a one-round launch in which units start up or drain.
+// compute unit (all that a unit's load path moves) at 128 x 128, 53 at 128 x 192.  Measured at 128 x 192, K = 8192, one workgroup per unit: MFMAs alone 367 ns a step,
+// with the fragment reads 480, with the loads 508, with both 635, before they were interleaved one by one (below): the parts added up instead of overlapping.
+// Now 8192 x 768, K = 32000 runs at 1.11 PFLOP/s (was 0.99), a 64 x 64 tile's step takes 180 ns (was 285).
 #include "pp_kernels.h"
 #include "pp_dev.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace pp {
@@ -30,21 +30,28 @@ template <int N> __device__ __forceinline__ void wait_vm_lgkm0() {          // v
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int NS>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_nt_ring_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
-                                                                    bf16_t* C, int ldc, int M, int N, int K, const bf16_t* R, int tiles_m, int tiles_n, int vec) {
-  constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, MI = TM / 16, NJ = TN / 16;
+// Where a K step's fragments come from (WHOLE):
+//   true: all fragments of step s + 1 are read while step s is multiplied (two whole sets of registers).  One wait and one barrier per step with the
+//     whole step's MFMAs between a read and its use: what a tile needs whose MFMAs alone are shorter than two trips to LDS (64 x 64: 8 per wave).
+//   false: half a step (32 of K) ahead, half the registers, so that 64 x 48 and 64 x 64 per wave fit without spilling.
+// In both forms every fragment read and every load stands behind an MFMA of its own (Items).  With a step's loads issued in one go the waves sat in the
+// memory pipeline's queue (16 cycles a load, 40 loads a step at 128 x 192) ahead of their own MFMAs, and the compiler waited for the reads of the NEXT half
+// step in front of the current one's MFMAs.  us, before / now: 8192 x 768, K = 32000 408 / 361; 2048 x 2048, K = 2048 21.9 / 17.0 (128 x 128); 3055 x 768, K = 3072 25.6 /
+// 21.0 (64 x 96 / 128 x 128); 1003 x 768, K = 768 6.2 / 5.3 (64 x 64); 500 x 2048, K = 8192 40.6 / 27.0 (64 x 64, three / four stages).
+template <int EPI, int BM, int BN, int WM, int WN, int NS, bool WHOLE, bool TOUCH>
+__global__ __launch_bounds__(64 * WM * WN, WHOLE ? 1 : 2) void gemm_nt_ring_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
+                                                                         bf16_t* C, int ldc, int M, int N, int K, const bf16_t* R, int tiles_m, int tiles_n, int vec, int touch) {
+  constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, MI = TM / 16, NJ = TN / 16, FR = MI + NJ;
   constexpr int STAGE = (BM + BN) * 128, LPW = (BM + BN) / 8 / NW;          // bytes of a stage; wave-loads (8 rows) per wave
   constexpr int PITCH = TN * 4 + 16;                                         // epilogue patch: bytes per row
-  static_assert((BM + BN) / 8 % NW == 0 && TM % 16 == 0 && TN % 16 == 0 && MI % 2 == 0 && NW * 32 * PITCH <= NS * STAGE, "tile geometry");
+  static_assert((BM + BN) / 8 % NW == 0 && TM % 16 == 0 && TN % 16 == 0 && MI % 2 == 0 && NW * 32 * PITCH <= NS * STAGE && NS >= 2, "tile geometry");
   extern __shared__ __align__(16) unsigned char r_lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   // XCD k = id % 8 owns a contiguous range of the tile list, ordered in groups of 8 M-tiles by all N-tiles
-  const int nb = tiles_m * tiles_n;
-  int pid = blockIdx.x;
-  if ((nb & 7) == 0) pid = (pid & 7) * (nb >> 3) + (pid >> 3);
+  const int nb = tiles_m * tiles_n, xcd = blockIdx.x & 7;
+  const int pid = xcd * (nb >> 3) + min(xcd, nb & 7) + (blockIdx.x >> 3);          // the first nb % 8 XCDs have one tile more
   constexpr int GROUP = 8;
   const int per_group = GROUP * tiles_n;
   const int group = pid / per_group, first_m = group * GROUP;
@@ -60,57 +67,132 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_ring_kernel(const bf16_t
     const int row = (wave + NW * i) * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
     g[i] = row < BM ? A + (size_t)min(m0 + row, M - 1) * lda + c * 8 : B + (size_t)min(n0 + row - BM, N - 1) * ldb + c * 8;
   }
-  auto issue = [&](int s, int slot) {
-    unsigned char* dst = r_lds + slot * STAGE + wave * 1024;
-#pragma unroll
-    for (int i = 0; i < LPW; ++i) __builtin_amdgcn_global_load_lds(PP_R_GPTR(g[i] + (size_t)s * 64), PP_R_LPTR(dst + i * NW * 1024), 16, 0, 0);
+  auto load1 = [&](int i, int s, int slot) {          // wave-load i of stage s
+    __builtin_amdgcn_global_load_lds(PP_R_GPTR(g[i] + (size_t)s * 64), PP_R_LPTR(r_lds + slot * STAGE + wave * 1024 + i * NW * 1024), 16, 0, 0);
   };
 
-  // ---- fragments: lane l reads, for row l % 16 of a 16-row block, the 8 k 8 (l / 16) .. of K32 slice kk
+  // ---- fragments: lane l reads, for row l % 16 of a 16-row block, the 8 k 8 (l / 16) .. of K32 slice kk; x counts NJ blocks of B, then MI of A
+  constexpr int SETS = WHOLE ? 4 : 2;          // sets of one K32 slice each
   const int l16 = lane & 15, lq = lane >> 4, sw = (l16 >> 1) & 7;
   const int fa0 = (wm * TM + l16) * 128, fb0 = (BM + wn * TN + l16) * 128;
-  bf16x8 fa[2][MI], fb[2][NJ];
-  auto read = [&](int buf, int slot, int kk) {
-    const unsigned char* p = r_lds + slot * STAGE + (((4 * kk + lq) ^ sw) << 4);
-#pragma unroll
-    for (int i = 0; i < MI; ++i) fa[buf][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p + fa0 + i * 2048));
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) fb[buf][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p + fb0 + j * 2048));
+  bf16x8 fa[SETS][MI], fb[SETS][NJ];
+  auto read1 = [&](int set, const unsigned char* st, int kk, int x) {
+    const unsigned char* p = st + (((4 * kk + lq) ^ sw) << 4);
+    if (x < NJ) fb[set][x] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p + fb0 + x * 2048));
+    else fa[set][x - NJ] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p + fa0 + (x - NJ) * 2048));
   };
   f32x4 acc[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto mm = [&](int buf) {
+  // NM MFMAs (of slices SET, SET + 1, ..) with the NI items of `item` behind them, as early as one per MFMA allows
+  auto run = [&](auto SET_, auto NM_, auto NI_, auto item) {
+    constexpr int SET = decltype(SET_)::value, NM = decltype(NM_)::value, NI = decltype(NI_)::value, DEN = NI < NM ? NI : NM;
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int x = 0; x < NM; ++x) {
+      const int set = SET + x / (MI * NJ), y = x % (MI * NJ);
+      acc[y / NJ][y % NJ] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][y % NJ], fa[set][y / NJ], acc[y / NJ][y % NJ], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (x < DEN) {
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[buf][j], fa[buf][i], acc[i][j], 0, 0, 0);
+        for (int it = x * NI / DEN; it < (x + 1) * NI / DEN; ++it) item(it);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   };
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-    if (s < ns) issue(s, s);
-  if (ns >= NS) wait_vm_lgkm0<(NS - 1) * LPW>(); else wait_vm_lgkm0<0>();
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  read(0, 0, 0);
-  int slot = 0;
-  for (int s = 0; s < ns; ++s) {
-    const int nxt = slot + 1 == NS ? 0 : slot + 1;
-    read(1, slot, 1);
-    mm(0);
-    __builtin_amdgcn_sched_barrier(0);
-    // this wave's rows of stage s + 1 have landed and its fragments of stage s are in registers; behind the barrier that holds for all
-    if (s + NS <= ns) wait_vm_lgkm0<(NS - 2) * LPW>(); else wait_vm_lgkm0<0>();
+  auto meet = [&](auto PENDING_) {          // all but this wave's newest loads have landed, its fragment reads too; then everybody's have
+    wait_vm_lgkm0<decltype(PENDING_)::value>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    if (s + NS < ns) issue(s + NS, slot);
-    if (s + 1 < ns) read(0, nxt, 0);
-    mm(1);
+  };
+  // Stage s + NS is requested into the slot of stage s once that is in everybody's registers: WHOLE, all of it behind the barrier that opens step s; else
+  // its first LB loads behind the barrier in the middle of step s, the other LA in the first half of step s + 1.
+  constexpr int LB = WHOLE ? LPW : LPW - LPW / 2, LA = LPW - LB;
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, (NS - 2) * LPW> Steady;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    if (s < ns) {
+#pragma unroll
+      for (int i = 0; i < (s == NS - 1 ? LB : LPW); ++i) load1(i, s, s);
+    }
+  // B in the order it lies in memory: the first `touch` * (threads of the grid) of its 128-byte pieces, one word each, on their way into the caches while the
+  // first stages arrive.  A step asks for 128 bytes of every row of B at once, K elements apart, and where B comes from HBM (a weight that the pass uses
+  // once) those lie in few channels: 3055 x 768 with a B out of cache took 27.5 us at K = 3072 and 51.8 at K = 6144, with the words 22.7 and 41.2.
+  uint32_t word[4] = {0, 0, 0, 0};
+  if constexpr (TOUCH) {
+    const uint32_t per_row = K / 64, last = (uint32_t)N * per_row - 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q < touch) {
+        const uint32_t id = min((q * gridDim.x + blockIdx.x) * (64u * NW) + tid, last), row = id / per_row;
+        word[q] = *reinterpret_cast<const uint32_t*>(B + (size_t)row * ldb + (id - row * per_row) * 64);
+      }
     __builtin_amdgcn_sched_barrier(0);
-    slot = nxt;
   }
+  if (ns >= NS) meet(std::integral_constant<int, (NS - 2) * LPW + LB>{});
+  else if (NS > 3 && ns == 3) meet(std::integral_constant<int, 2 * LPW>{});
+  else if (ns == 2) meet(std::integral_constant<int, LPW>{});
+  else meet(I0{});
+#pragma unroll
+  for (int x = 0; x < (WHOLE ? 2 : 1) * FR; ++x) read1(x / FR, r_lds, x / FR, x % FR);
+  int slot = 0, prev = NS - 1, s = 0;
+  if constexpr (WHOLE) {
+    // the step of fragment sets BUF, BUF + 1; RD: the other two sets take stage s + 1
+    auto step = [&](auto BUF_, auto RD_, auto LD_) {
+      constexpr int BUF = decltype(BUF_)::value, NR = decltype(RD_)::value * 2 * FR, LD = decltype(LD_)::value;
+      const int nxt = slot + 1 == NS ? 0 : slot + 1;
+      const unsigned char* st = r_lds + nxt * STAGE;
+      run(BUF_, std::integral_constant<int, 2 * MI * NJ>{}, std::integral_constant<int, NR + LD * LPW>{},
+          [&](int it) { if (it < NR) read1(2 - BUF + it / FR, st, it / FR, it % FR); else load1(it - NR, s + NS, slot); });
+      slot = nxt; ++s;
+    };
+    typedef std::integral_constant<int, 2> I2;
+    while (s + 1 + NS < ns) {
+      meet(Steady{}); step(I0{}, I1{}, I1{});
+      meet(Steady{}); step(I2{}, I1{}, I1{});
+    }
+    auto tail = [&](auto BUF_) {          // at most NS + 1 steps
+      const bool ld = s + NS < ns;
+      if (s + NS <= ns) meet(Steady{});
+      else if (NS >= 4 && s + NS - 1 <= ns) meet(std::integral_constant<int, (NS >= 4 ? NS - 3 : 0) * LPW>{});
+      else meet(I0{});
+      if (ld) step(BUF_, I1{}, I1{});
+      else if (s + 1 < ns) step(BUF_, I1{}, I0{});
+      else step(BUF_, I0{}, I0{});
+    };
+    for (;;) {
+      tail(I0{});
+      if (s == ns) break;
+      tail(I2{});
+      if (s == ns) break;
+    }
+  } else {
+    auto half = [&](auto BUF_, auto RD_, auto LD_, int rslot, int ls, int lslot) {          // slice BUF of step s; RD: the other set takes the slice behind it
+      constexpr int BUF = decltype(BUF_)::value, NR = decltype(RD_)::value * FR, NLD = decltype(LD_)::value ? (BUF ? LB : LA) : 0;
+      const unsigned char* st = r_lds + rslot * STAGE;
+      __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): this slice's fragments (the only reads in flight)
+      __builtin_amdgcn_sched_barrier(0);
+      run(BUF_, std::integral_constant<int, MI * NJ>{}, std::integral_constant<int, NR + NLD>{},
+          [&](int it) { if (it < NR) read1(1 - BUF, st, 1 - BUF, it); else load1((BUF ? 0 : LB) + it - NR, ls, lslot); });
+    };
+    auto step = [&](auto RD_, auto LDA_, auto LDB_, auto PENDING_) {          // RD: there is a step s + 1
+      const int nxt = slot + 1 == NS ? 0 : slot + 1;
+      half(I0{}, I1{}, LDA_, slot, s + NS - 1, prev);
+      meet(PENDING_);
+      half(I1{}, RD_, LDB_, nxt, s + NS, slot);
+      prev = slot; slot = nxt; ++s;
+    };
+    while (s < ns - NS) step(I1{}, I1{}, I1{}, Steady{});
+    if (ns >= NS) step(I1{}, I1{}, I0{}, Steady{});          // s = ns - NS: the other loads of the last stage
+    if (NS > 3 && s + 3 == ns) step(I1{}, I0{}, I0{}, std::integral_constant<int, LPW>{});
+    while (s < ns - 1) step(I1{}, I0{}, I0{}, I0{});
+    step(I0{}, I0{}, I0{}, I0{});
+  }
+
+  if constexpr (TOUCH) asm volatile("" ::"v"(word[0]), "v"(word[1]), "v"(word[2]), "v"(word[3]));          // loaded for their lines only
 
   // ---- epilogue: nothing is in flight and nobody reads the stages any more (the last barrier).  Element r of block (i, j) is row
   // 16 i + l % 16, column 16 j + 4 (l / 16) + r of the wave's TM x TN part; it is turned around in a private patch.
@@ -169,55 +251,72 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_ring_kernel(const bf16_t
   }
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int NS>
+template <int EPI, int BM, int BN, int WM, int WN, int NS, bool WHOLE, bool TOUCH = false>
 static int launch_ring(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const void* R) {
   constexpr int LDS = NS * (BM + BN) * 128;
-  auto kern = gemm_nt_ring_kernel<EPI, BM, BN, WM, WN, NS>;
+  auto kern = gemm_nt_ring_kernel<EPI, BM, BN, WM, WN, NS, WHOLE, TOUCH>;
   static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS) == hipSuccess;
   if (!ok) return 1;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   // columns per store: with 2-byte stores only, 4096 x 2044, K = 64 took 18.2 us against 10.1 of the 8-byte stores of 128 x 128 tiles
   const uintptr_t al = (uintptr_t)C | (uintptr_t)R;
   const int vec = ((N | ldc) & 7) == 0 && (al & 15) == 0 ? 8 : ((N | ldc) & 3) == 0 && (al & 7) == 0 ? 4 : 1;
-  kern<<<dim3(tiles_m * tiles_n), 64 * WM * WN, LDS, st>>>((const bf16_t*)A, lda, (const bf16_t*)B, ldb, (bf16_t*)C, ldc, M, N, K, (const bf16_t*)R, tiles_m, tiles_n, vec);
+  const long threads = (long)tiles_m * tiles_n * 64 * WM * WN, pieces = (long)N * (K / 64);
+  const int touch = TOUCH ? (int)std::min(4l, (pieces + threads - 1) / threads) : 0;          // words of B per thread
+  kern<<<dim3(tiles_m * tiles_n), 64 * WM * WN, LDS, st>>>((const bf16_t*)A, lda, (const bf16_t*)B, ldb, (bf16_t*)C, ldc, M, N, K, (const bf16_t*)R, tiles_m, tiles_n, vec, touch);
   return 0;
 }
-// The tiles, with what one K step of 64 was measured to take (ns) when 1, 2, .. workgroups share a compute unit, and the cost of a
-// workgroup outside its main loop (launch, first loads, epilogue).  The times come from M = 1003 .. 8192, N = 640 .. 8192, K = 768 .. 32000; the
-// model picks the fastest of the five or one within 5 % of it on all of them.
-struct RingTile { int bm, bn, per_cu, step[3], over; };
-static const RingTile kTiles[] = {
-    {64, 64, 3, {330, 440, 560}, 1400},          // 4 waves of 32 x 32, three stages: 48 KB, three workgroups per unit
-    {64, 96, 2, {360, 480, 0}, 1600},            // 4 waves of 32 x 48, three stages: 60 KB, two
-    {128, 128, 1, {530, 0, 0}, 1600},            // 8 waves of 64 x 32, four stages: 128 KB
-    {128, 192, 1, {700, 0, 0}, 1600},            // 8 waves of 64 x 48, three stages: 120 KB (four stages: 2-5 % slower)
-    {256, 128, 1, {840, 0, 0}, 1600},            // 8 waves of 64 x 64, three stages: 144 KB
+// The tiles, with what was measured of each (ns): one K step of 64 when 1, 2, .. workgroups share a compute unit and every unit has one; the part of
+// that by which it is shorter on a nearly idle chip (%); a workgroup outside its main loop (first loads, epilogue) in a last round of fewer workgroups per unit
+// and in a full one.  Fitted to 170 shapes, M = 32 .. 16384, N = 64 .. 16384, K = 64 .. 32000, with A in cache and B (the weight) out of it; over those the tile that
+// the model picks takes 2 % longer than the best one on average.
+struct RingTile { int bm, bn, per_cu, step[3], idle, over, over_full; };
+static constexpr RingTile kTiles[] = {
+    {32, 64, 3, {205, 271, 414}, 26, 1668, 1243},         // 2 waves of 32 x 32, four stages: 48 KB, three workgroups per unit
+    {64, 64, 2, {216, 371, 0}, 19, 1724, 1483},           // 4 waves of 32 x 32, four stages: 64 KB, two
+    {64, 96, 2, {286, 456, 0}, 25, 1737, 1956},           // 4 waves of 32 x 48, four stages: 80 KB, two
+    {64, 128, 1, {316, 0, 0}, 20, 0, 1604},               // 8 waves of 32 x 32, four stages: 96 KB
+    {64, 192, 1, {426, 0, 0}, 35, 0, 1849},               // 8 waves of 32 x 48, four stages: 128 KB
+    {128, 128, 1, {493, 0, 0}, 42, 0, 1952},              // 8 waves of 64 x 32, four stages: 128 KB
+    {128, 192, 1, {682, 0, 0}, 55, 0, 2446},              // 8 waves of 64 x 48, three stages: 120 KB
+    {128, 256, 1, {874, 0, 0}, 56, 0, 2732},              // 8 waves of 64 x 64, three stages: 144 KB
 };
 // Which tile: a launch lasts as long as the compute units with the most workgroups, so the tile that divides M x N into full
-// rounds of 256 units usually wins over the one with the best rate.  us before (128 x 128 tiles, 4 waves of 64 x 64, two stages) / now: 8192 x 768,
-// K = 768 21.9 / 16.6, K = 3072 51 / 41, K = 32000 539 / 413 (128 x 192); 3055 x 768, K = 3072 35.9 / 27.0 (64 x 96); 1003 x 768, K = 768 10.4 / 6.3
-// (64 x 64); 2048 x 2048, K = 2048 27.7 / 23.3 (128 x 128); 4096 x 2048, K = 2048 41.1 / 36.3 (256 x 128).
-static int ring_tile(int M, int N, int K) {
-  int best = 0;
-  long t_best = -1;
-  for (int v = 0; v < 5; ++v) {
-    const RingTile& t = kTiles[v];
-    const long per_unit = ((long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) + 255) / 256;
-    const long full = per_unit / t.per_cu, rest = per_unit % t.per_cu, steps = K / 64;
-    const long cost = full * (steps * t.step[t.per_cu - 1] + t.over * 13 / 10) + (rest ? steps * t.step[rest - 1] + t.over : 0);
-    if (t_best < 0 || cost < t_best) { t_best = cost; best = v; }
+// rounds of 256 units usually wins over the one with the best rate.  Unrolled over the table, so that nothing is divided at run time (this runs for
+// every call; as a loop over the table it took 0.2 of the 4 us that a call takes on the host).
+template <int V = 0>
+static int ring_tile(unsigned M, unsigned N, unsigned steps, int best = 0, long best_cost = 0x7fffffffffffffffl) {
+  if constexpr (V < (int)(sizeof(kTiles) / sizeof(kTiles[0]))) {
+    constexpr RingTile t = kTiles[V];
+    const unsigned tiles = (M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn), per_unit = (tiles + 255) / 256;
+    const unsigned full = per_unit / t.per_cu, rest = per_unit % t.per_cu;
+    const long step = (long)steps * (tiles >= 256 ? 25600 : 25600 - t.idle * (256 - tiles));          // in 1 / 25600
+    const long cost = (long)full * (step * t.step[t.per_cu - 1] / 25600 + t.over_full) + (rest ? step * t.step[rest - 1] / 25600 + t.over : 0);
+    return cost < best_cost ? ring_tile<V + 1>(M, N, steps, V, cost) : ring_tile<V + 1>(M, N, steps, best, best_cost);
   }
   return best;
 }
 
+// B is touched ahead from K = 2048 on, by the tiles of one workgroup per unit: below that it costs what it saves (3055 x 768, K = 768: 8.3 us without, 8.5 with; its
+// code alone 0.5 of the 4.3 us of a K of 64), and the tiles of several workgroups per unit, which are at different K already, lose as often as they gain (3055 x 768 in
+// 64 x 96 tiles, K = 3072: 24.7 / 27.8).
+template <int EPI, int BM, int BN, int NS>
+static int launch_half(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const void* R) {
+  if (K >= 2048 && (long)N * (K / 64) < (1l << 31)) return launch_ring<EPI, BM, BN, 2, 4, NS, false, true>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+  return launch_ring<EPI, BM, BN, 2, 4, NS, false>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+}
+
 template <int EPI>
 static int dispatch_ring(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const void* R) {
-  switch (ring_tile(M, N, K)) {
-    case 0: return launch_ring<EPI, 64, 64, 2, 2, 3>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
-    case 1: return launch_ring<EPI, 64, 96, 2, 2, 3>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
-    case 2: return launch_ring<EPI, 128, 128, 2, 4, 4>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
-    case 3: return launch_ring<EPI, 128, 192, 2, 4, 3>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
-    default: return launch_ring<EPI, 256, 128, 4, 2, 3>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+  switch (ring_tile(M, N, K / 64)) {
+    case 0: return launch_ring<EPI, 32, 64, 1, 2, 4, true>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+    case 1: return launch_ring<EPI, 64, 64, 2, 2, 4, true>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+    case 2: return launch_ring<EPI, 64, 96, 2, 2, 4, true>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+    case 3: return launch_half<EPI, 64, 128, 4>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+    case 4: return launch_half<EPI, 64, 192, 4>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+    case 5: return launch_half<EPI, 128, 128, 4>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+    case 6: return launch_half<EPI, 128, 192, 3>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
+    default: return launch_half<EPI, 128, 256, 3>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
   }
 }
 

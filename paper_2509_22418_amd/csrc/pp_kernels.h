@@ -103,7 +103,7 @@ int k_gemm_nt_mfma(hipStream_t st, const void* A, int lda, const void* B, int ld
 // shape is not taken.
 int k_gemm_tn_mfma(hipStream_t st, const void* A, int lda, int m_blk, long a_blk_stride, const void* B, int ldb, float* C, int ldc,
                    int M, int N, int K, int kchunk, float* partial, int sub = 0x40000000);          // sub: rows per running fp32 sum (a multiple of 64)
-// smaller tiles (64 x 64 to 256 x 128, chosen by shape) for shapes with too few 256 x 256 tiles to fill the chip (bf16 out, EPI_STORE / EPI_ADD_RES)
+// smaller tiles (32 x 64 to 128 x 256, chosen by shape) for shapes with too few 256 x 256 tiles to fill the chip (bf16 out, EPI_STORE / EPI_ADD_RES)
 int k_gemm_nt_ring(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, int epi, const void* R);
 void gemm_set_small_tiles(int v);      // 1 (default): k_gemm_nt_mfma hands GEMMs with at most 128 tiles of 256 x 256 (half a tile per compute unit) to k_gemm_nt_ring
 void gemm_set_variant(int v);          // 0: register-staged MFMA GEMM, 1: direct-to-LDS MFMA GEMM
