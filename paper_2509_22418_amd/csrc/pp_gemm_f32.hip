@@ -21,7 +21,7 @@
 // multiples of 4.  An NT panel row is cut into groups of 8 (16) k; the 16-byte chunk i of a group holds the k
 // that lane group i needs (k = i mod 2, resp. mod 4), so one 16-byte read feeds four MFMAs.  Chunks are permuted by row so that 16
 // rows of one chunk lie on different banks; all the same a third of the kernel's LDS-active cycles are counted as conflicts (LDS active 0.31 to 0.40, matrix pipe
-// busy 0.53 with 32 x 32 tiles, 0.81 with 64 x 64: profiles/op_kernels_pmc.txt).  TN panels are stored [k][m] as they lie
+// busy 0.53 with 32 x 32 tiles without DEEP, 0.81 with 64 x 64: profiles/op_kernels_pmc.txt).  TN panels are stored [k][m] as they lie
 // in memory, with bit 5 (bit 4) of m flipped for every second k (pair of k), and are read 4 bytes per lane.
 #include "pp_kernels.h"
 #include "pp_dev.h"
@@ -60,7 +60,8 @@ struct F32GemmArgs {
 };
 
 // VEC: groups of four elements are aligned and exist as a whole
-template <class T, class TO, bool TN, bool SMALL, bool VEC>
+// DEEP: fragments one step ahead (see step below)
+template <class T, class TO, bool TN, bool SMALL, bool VEC, bool DEEP>
 __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const T* __restrict__ A, const T* __restrict__ B, TO* C, const T* R, const F32GemmArgs g) {
   constexpr int BM = SMALL ? 32 : 64, BK = SMALL ? 64 : 32;
   constexpr int CPR = BK / 4;                              // NT: 16-byte chunks per panel row
@@ -141,60 +142,122 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const T* __restrict_
     if constexpr (SMALL) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
     else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
   };
-  auto compute = [&](int stage) {
-    const float* sa = lds + stage * 2 * PANEL;
-    const float* sb = sa + PANEL;
-    constexpr int G = SMALL ? 4 : 2;          // k per MFMA
-    if constexpr (TN) {
-#pragma unroll
-      for (int h = 0; h < BK / G; h += 16) {
-        float fa[16], fb[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int k = (h + j) * G + lg;
-          fa[j] = sa[k * BM + tcol(k, wm + lr)];
-          fb[j] = sb[k * BM + tcol(k, wn + lr)];
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) mfma(fa[j], fb[j]);
-      }
-    } else {
-      const int ra = wm + lr, rb = wn + lr;
-#pragma unroll
-      for (int h = 0; h < CPR / G; h += 4) {
-        float4 fa[4], fb[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          fa[i] = *reinterpret_cast<const float4*>(sa + at(ra, (h + i) * G + lg));
-          fb[i] = *reinterpret_cast<const float4*>(sb + at(rb, (h + i) * G + lg));
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { mfma(fa[i].x, fb[i].x); mfma(fa[i].y, fb[i].y); mfma(fa[i].z, fb[i].z); mfma(fa[i].w, fb[i].w); }
-      }
-    }
-  };
-  // ---- main loop: step s is multiplied from stage s & 1 while step s + 1 goes from registers to the other stage and step
-  // s + 2 is requested; one barrier per step
   float4 a0[NV], b0[NV], a1[NV], b1[NV];
-  load(a0, b0, 0);
-  load(a1, b1, 1);
-  store(a0, b0, 0);
-  __syncthreads();
-  for (int s = 0; s + 1 < nk; s += 2) {
-    load(a0, b0, s + 2);
-    __builtin_amdgcn_sched_barrier(0);          // the requests leave before the MFMAs, not after them
-    compute(0);
-    __builtin_amdgcn_sched_barrier(0);
-    store(a1, b1, 1);
-    __syncthreads();
-    load(a1, b1, s + 3);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(1);
-    __builtin_amdgcn_sched_barrier(0);
+  if constexpr (DEEP) {
+    static_assert(!DEEP || !TN, "fragments of K-contiguous panels");
+    // ---- a step is 16 MFMAs, k ascending; its fragments are in registers when it starts
+    constexpr int G = SMALL ? 4 : 2;          // k per MFMA
+    float fa[2][16], fb[2][16];
+    auto read = [&](int set, int stage, int j) {          // operands of MFMAs 4 j .. 4 j + 3
+      const float* sa = lds + stage * 2 * PANEL;
+      *reinterpret_cast<float4*>(fa[set] + 4 * j) = *reinterpret_cast<const float4*>(sa + at(wm + lr, j * G + lg));
+      *reinterpret_cast<float4*>(fb[set] + 4 * j) = *reinterpret_cast<const float4*>(sa + PANEL + at(wn + lr, j * G + lg));
+    };
+    auto meet = [&]() {          // this wave's LDS accesses are done, then everybody's; loads stay in flight
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // Step s, with everything else that happens meanwhile spread behind its MFMAs: the fragments of step s + 1, step s + 2 from
+    // registers into the slot that step s was read from, the requests of step s + 4 into those registers.  One barrier per step.
+    // (With the step's own fragments read in front of its MFMAs and the panels stored behind them the matrix pipe was busy 0.53 of the time with
+    // 32 x 32 tiles, two workgroups per unit: 1024 x 512, K = 2048 31 us.)
+    auto step = [&](int set, float4 (&ra)[NV], float4 (&rb)[NV], int s) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        mfma(fa[set][j], fb[set][j]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (j < 4) read(1 - set, 1 - set, j);
+        if (j >= 4 && j < 4 + 4 * NV && (j & 3) == 0) {
+          const int i = j / 4 - 1;
+          float* d = lds + set * 2 * PANEL;
+          put_piece(d, i, ra[i]); put_piece(d + PANEL, i, rb[i]);
+        }
+        if (j == 4 + 4 * NV - 3) load(ra, rb, s + 4);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      meet();
+    };
+    load(a0, b0, 0);
+    load(a1, b1, 1);
+    store(a0, b0, 0);
+    if (nk > 1) {
+      load(a0, b0, 2);
+      store(a1, b1, 1);
+      load(a1, b1, 3);
+    }
+    meet();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) read(0, 0, j);
+    if (nk > 1) meet();
+    int s = 0;
+    for (; s + 2 < nk; s += 2) {
+      step(0, a0, b0, s);
+      step(1, a1, b1, s + 1);
+    }
+    if (s + 1 < nk) {
+      step(0, a0, b0, s);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) mfma(fa[1][j], fb[1][j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) mfma(fa[0][j], fb[0][j]);
+    }
+  } else {
+    auto compute = [&](int stage) {
+      const float* sa = lds + stage * 2 * PANEL;
+      const float* sb = sa + PANEL;
+      constexpr int G = SMALL ? 4 : 2;          // k per MFMA
+      if constexpr (TN) {
+#pragma unroll
+        for (int h = 0; h < BK / G; h += 16) {
+          float fa[16], fb[16];
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const int k = (h + j) * G + lg;
+            fa[j] = sa[k * BM + tcol(k, wm + lr)];
+            fb[j] = sb[k * BM + tcol(k, wn + lr)];
+          }
+#pragma unroll
+          for (int j = 0; j < 16; ++j) mfma(fa[j], fb[j]);
+        }
+      } else {
+        const int ra = wm + lr, rb = wn + lr;
+#pragma unroll
+        for (int h = 0; h < CPR / G; h += 4) {
+          float4 fa[4], fb[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            fa[i] = *reinterpret_cast<const float4*>(sa + at(ra, (h + i) * G + lg));
+            fb[i] = *reinterpret_cast<const float4*>(sb + at(rb, (h + i) * G + lg));
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) { mfma(fa[i].x, fb[i].x); mfma(fa[i].y, fb[i].y); mfma(fa[i].z, fb[i].z); mfma(fa[i].w, fb[i].w); }
+        }
+      }
+    };
+    // ---- main loop: step s is multiplied from stage s & 1 while step s + 1 goes from registers to the other stage and step
+    // s + 2 is requested; one barrier per step
+    load(a0, b0, 0);
+    load(a1, b1, 1);
     store(a0, b0, 0);
     __syncthreads();
+    for (int s = 0; s + 1 < nk; s += 2) {
+      load(a0, b0, s + 2);
+      __builtin_amdgcn_sched_barrier(0);          // the requests leave before the MFMAs, not after them
+      compute(0);
+      __builtin_amdgcn_sched_barrier(0);
+      store(a1, b1, 1);
+      __syncthreads();
+      load(a1, b1, s + 3);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(1);
+      __builtin_amdgcn_sched_barrier(0);
+      store(a0, b0, 0);
+      __syncthreads();
+    }
+    if (nk & 1) compute(0);
   }
-  if (nk & 1) compute(0);
 
   // ---- epilogue: 32 x 32: element r of a lane is row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32; 16 x 16: row 4 (lane / 16) + r
   C += (size_t)z * (size_t)g.M * (size_t)g.ldc;          // split-K partials are dense [z][M][ldc]
@@ -216,13 +279,25 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const T* __restrict_
 // (1024 x 512 x 2048 on the vector-FMA kernel: 212 us; 4096 x 4096 x 1024: 286 us = 120 TFLOP/s.)
 constexpr long kLargeTiles = 512;
 
+// Up to kDeepTiles 32 x 32 tiles of fp32 K-contiguous operands the fragments are read a step ahead (DEEP, 132 registers a wave): with one or two workgroups per
+// unit nothing else covers the reads and stores of a step.  us without / with: 1024 x 512 (512 tiles), K = 2048 32.1 / 26.3, K = 8000 101 / 80.5; 1024 x 1536 (1536), K = 512
+// 19.7 / 18.7; from there on the workgroups that the registers cost are worth more: 1024 x 2048 (2048) 23.2 / 24.2, and so they are with 64 x 64 tiles
+// (1024 x 4096, K = 512 39.7 / 49.1, 168 registers).  Short ranges lose to the longer code (128 x 64, K = 64 3.8 / 4.2; K = 256 4.3 / 4.0), token-major panels, read four bytes at a
+// time, gain nothing (512 x 512 over 1024 in ranges of 256: 9.9 / 10.6), and widened bf16 operands would be waited for right behind their requests (1000 x 520, K = 1000 21.7 / 23.2).
+constexpr long kDeepTiles = 1536;
+constexpr int kDeepRange = 256;
+
 template <class T, class TO, bool TN, bool VEC>
 static void launch_f32(hipStream_t st, const void* A, const void* B, void* C, const void* R, const F32GemmArgs& g, int splits) {
   const long t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * splits;
+  constexpr bool kDeep = sizeof(T) == 4 && !TN;
+  const dim3 grid32((g.N + 31) / 32, (g.M + 31) / 32, splits);
   if (t64 >= kLargeTiles)
-    gemm_f32_mfma_kernel<T, TO, TN, false, VEC><<<dim3((g.N + 63) / 64, (g.M + 63) / 64, splits), 256, 0, st>>>((const T*)A, (const T*)B, (TO*)C, (const T*)R, g);
+    gemm_f32_mfma_kernel<T, TO, TN, false, VEC, false><<<dim3((g.N + 63) / 64, (g.M + 63) / 64, splits), 256, 0, st>>>((const T*)A, (const T*)B, (TO*)C, (const T*)R, g);
+  else if (kDeep && (long)grid32.x * grid32.y * grid32.z <= kDeepTiles && g.kchunk >= kDeepRange)
+    gemm_f32_mfma_kernel<T, TO, TN, true, VEC, kDeep><<<grid32, 256, 0, st>>>((const T*)A, (const T*)B, (TO*)C, (const T*)R, g);
   else
-    gemm_f32_mfma_kernel<T, TO, TN, true, VEC><<<dim3((g.N + 31) / 32, (g.M + 31) / 32, splits), 256, 0, st>>>((const T*)A, (const T*)B, (TO*)C, (const T*)R, g);
+    gemm_f32_mfma_kernel<T, TO, TN, true, VEC, false><<<grid32, 256, 0, st>>>((const T*)A, (const T*)B, (TO*)C, (const T*)R, g);
 }
 template <class T, class TO, bool TN>
 static void launch_f32(hipStream_t st, const void* A, const void* B, void* C, const void* R, const F32GemmArgs& g, int splits, bool vec) {
