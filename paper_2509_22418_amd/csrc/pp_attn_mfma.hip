@@ -358,148 +358,163 @@ __device__ __forceinline__ void unrotate_tile(f32x16 (&acc)[DH / 32], const floa
 // S^T = K Q^T, dP^T = V dO^T, dS^T = P^T * (dP^T - D), dQ^T += K^T dS^T (K^T gathered from the K rows by transpose reads).
 // The kernel also forms D = rowsum(dO * O) for its queries (each lane already holds half of its query's dO row) and
 // stores it in Dbuf for the dK/dV kernel, which runs after it.
+// part of D: 8 products of one 16-byte piece of dO and O, in order
+__device__ __forceinline__ float d_piece(const u32x4& dw, const u32x4& ow, float D) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    D = fmaf(__uint_as_float(dw[e] << 16), __uint_as_float(ow[e] << 16), D);
+    D = fmaf(__uint_as_float(dw[e] & 0xffff0000u), __uint_as_float(ow[e] & 0xffff0000u), D);
+  }
+  return D;
+}
+template <int DH, int NW, bool READ_D>
+__device__ __forceinline__ void attn_bwd_dq_block(u32x4* lds, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ dO,
+                                                  const float* __restrict__ lse, float* __restrict__ Dbuf, bf16_t* __restrict__ dqkv, int S, int h, int head, int b, int qblk,
+                                                  int lane, int wave, const float* __restrict__ cosb, const float* __restrict__ sinb) {
+  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8, QB = 32 * NW;
+  constexpr int K_CH = 64 * CPRK, ST_CH = 2 * K_CH;          // a stage = K rows, then V rows, of 64 keys
+  const int d = h * DH, ld = 3 * d;
+  const int l32 = lane & 31, lh = lane >> 5;
+  const uint32_t tr_off = tr_lane_off<CPRK>(lane);
+  const int q0 = qblk * QB, qw0 = q0 + wave * 32;
+  const int q = qw0 + l32, qc = min(q, S - 1);
+  const bf16_t* base = qkv + (size_t)b * S * ld + (size_t)head * DH;
+  const int n_tiles = min((q0 + QB + 63) / 64, (S + 63) / 64);
+  const float scale = 1.0f / sqrtf((float)DH), sc2 = LOG2E * scale;
+
+  bf16x8 qf[KS], dof[KS];
+  const size_t stat = ((size_t)b * h + head) * S + qc;
+  float Dq = 0.f;          // D of this lane's query: sum over the head dim of dO * O, lane halves hold alternate 8-element pieces
+  {
+    const bf16_t* qp = base + (size_t)qc * ld + 8 * lh;
+    const bf16_t* dp = dO + ((size_t)b * S + qc) * d + (size_t)head * DH + 8 * lh;
+    const bf16_t* op = o + ((size_t)b * S + qc) * d + (size_t)head * DH + 8 * lh;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * s));
+      const u32x4 dw = *reinterpret_cast<const u32x4*>(dp + 16 * s);
+      dof[s] = __builtin_bit_cast(bf16x8, dw);
+      if constexpr (!READ_D) Dq = d_piece(dw, *reinterpret_cast<const u32x4*>(op + 16 * s), Dq);
+    }
+  }
+  if constexpr (READ_D) Dq = Dbuf[stat];
+  else {
+    Dq += __shfl_xor(Dq, 32, 64);
+    if (lh == 0 && q < S) Dbuf[stat] = Dq;
+  }
+  const float nlse2 = -lse[stat] * LOG2E;
+  f32x16 dqacc[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) zero16(dqacc[c]);
+
+  auto ksrc = [&](int kv0) { return [=](int row, int c) { return base + (size_t)min(kv0 + row, S - 1) * ld + d + c * 8; }; };
+  auto vsrc = [&](int kv0) { return [=](int row, int c) { return base + (size_t)min(kv0 + row, S - 1) * ld + 2 * d + c * 8; }; };
+  auto issue_all = [&](u32x4* stage, int kv0) {
+    Stage<64, CPRK, NW>::issue(stage, wave, lane, ksrc(kv0));
+    Stage<64, CPRK, NW>::issue(stage + K_CH, wave, lane, vsrc(kv0));
+  };
+  issue_all(lds, 0);
+  stage_sync();
+
+  for (int j = 0; j < n_tiles; ++j) {
+    const u32x4* ktile = lds + (j & 1) * ST_CH;
+    const u32x4* vtile = ktile + K_CH;
+    u32x4* nxt = lds + ((j + 1) & 1) * ST_CH;
+    const int kv0 = j * 64, kvn = min(j + 1, n_tiles - 1) * 64;
+    issue_all(nxt, kvn);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      const int kg0 = kv0 + 32 * mt;
+      if (kg0 > qw0 + 31) continue;          // wave-uniform: every key of the group lies beyond every query of this wave
+      f32x16 sacc, dpacc;
+      zero16(sacc); zero16(dpacc);
+      {
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 kb[2], vb[2];
+        kb[0] = frag<CPRK>(ktile, mt * 32 + l32, lh); vb[0] = frag<CPRK>(vtile, mt * 32 + l32, lh);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          PP_STEP_BEGIN();
+          if (s + 1 < KS) {
+            kb[(s + 1) & 1] = frag<CPRK>(ktile, mt * 32 + l32, 2 * (s + 1) + lh);
+            vb[(s + 1) & 1] = frag<CPRK>(vtile, mt * 32 + l32, 2 * (s + 1) + lh);
+          }
+          sacc = MFMA(kb[s & 1], qf[s], sacc);
+          dpacc = MFMA(vb[s & 1], dof[s], dpacc);
+          PP_READS_THEN_MFMAS(2, 2);
+        }
+      }
+      if (kg0 + 31 > qw0) {          // wave-uniform: the group straddles the diagonal
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = kg0 + 8 * (r >> 2) + 4 * lh + (r & 3);
+          const float p = key > q ? 0.f : fast_exp2(fmaf(sacc[r], sc2, nlse2));
+          sacc[r] = p * (dpacc[r] - Dq);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sacc[r] = fast_exp2(fmaf(sacc[r], sc2, nlse2)) * (dpacc[r] - Dq);
+      }
+      bf16x8 dsf[2];
+      dsf[0] = pack8(sacc, 0); dsf[1] = pack8(sacc, 8);
+      {
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 tb[2];          // K^T block n % CT for the 16 keys 32 mt + 16 (n / CT) ..
+        const uint32_t ktl = launder(lds_byte_offset(ktile) + tr_off);
+        tb[0] = frag_tr<CPRK>(ktl, 32 * mt, 0);
+        tb[1] = frag_tr<CPRK>(ktl, 32 * mt + 16 * (1 / CT), 1 % CT);
+#pragma unroll
+        for (int sp = 0; sp < CT; ++sp) {          // two (u, c) steps per fence
+          PP_STEP_BEGIN();
+          bf16x8 cur0 = tb[0], cur1 = tb[1];
+          if (sp + 1 < CT) {
+            const int n0 = 2 * sp + 2, n1 = 2 * sp + 3;
+            const uint32_t kt2 = launder(ktl);
+            tb[0] = frag_tr<CPRK>(kt2, 32 * mt + 16 * (n0 / CT), n0 % CT);
+            tb[1] = frag_tr<CPRK>(kt2, 32 * mt + 16 * (n1 / CT), n1 % CT);
+          }
+          const int a0 = 2 * sp, a1 = 2 * sp + 1;
+          dqacc[a0 % CT] = MFMA(cur0, dsf[a0 / CT], dqacc[a0 % CT]);
+          dqacc[a1 % CT] = MFMA(cur1, dsf[a1 / CT], dqacc[a1 % CT]);
+          PP_READS_THEN_MFMAS(4, 2);
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    stage_sync();
+  }
+  if (q < S) {
+    unrotate_tile<DH>(dqacc, cosb, sinb, q, lh);          // dQ w.r.t. the un-rotated query (linear: commutes with the scale below)
+    bf16_t* op = dqkv + ((size_t)b * S + q) * ld + (size_t)head * DH + 4 * lh;
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        u32x2 w;
+        w[0] = pack_bf16x2(dqacc[c][4 * g] * scale, dqacc[c][4 * g + 1] * scale);
+        w[1] = pack_bf16x2(dqacc[c][4 * g + 2] * scale, dqacc[c][4 * g + 3] * scale);
+        *reinterpret_cast<u32x2*>(op + c * 32 + 8 * g) = w;
+      }
+  }
+}
+
 template <int DH, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                               const bf16_t* __restrict__ dO, const float* __restrict__ lse,
                                                               float* __restrict__ Dbuf, bf16_t* __restrict__ dqkv, int S, int h, int n_pairs, int n_blk,
                                                               const float* __restrict__ cosb, const float* __restrict__ sinb) {
-  constexpr int KS = DH / 16, CT = DH / 32, CPRK = DH / 8, QB = 32 * NW;
   constexpr bool PAIRED = NW == 8;
   extern __shared__ u32x4 lds[];
-  constexpr int K_CH = 64 * CPRK, ST_CH = 2 * K_CH;          // a stage = K rows, then V rows, of 64 keys
-  const int d = h * DH, ld = 3 * d;
   int pair, comb;
   if constexpr (PAIRED) causal_block_map(blockIdx.x, n_pairs, (n_blk + 1) / 2, pair, comb);
   else { pair = blockIdx.x % n_pairs; comb = blockIdx.x / n_pairs; }          // one block per workgroup, heaviest first
-  const int head = pair % h, b = pair / h;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, lh = lane >> 5;
-  const uint32_t tr_off = tr_lane_off<CPRK>(lane);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // a late (heavy) query block, then its early (light) mirror image: every workgroup costs the same
   for (int part = 0; part < (PAIRED ? 2 : 1); ++part) {
     const int qblk = part == 0 ? n_blk - 1 - comb : comb;
     if (part == 1 && qblk == n_blk - 1 - comb) break;
-    const int q0 = qblk * QB, qw0 = q0 + wave * 32;
-    const int q = qw0 + l32, qc = min(q, S - 1);
-    const bf16_t* base = qkv + (size_t)b * S * ld + (size_t)head * DH;
-    const int n_tiles = min((q0 + QB + 63) / 64, (S + 63) / 64);
-    const float scale = 1.0f / sqrtf((float)DH), sc2 = LOG2E * scale;
-
-    bf16x8 qf[KS], dof[KS];
-    float Dq = 0.f;          // D of this lane's query: sum over the head dim of dO * O, lane halves hold alternate 8-element pieces
-    {
-      const bf16_t* qp = base + (size_t)qc * ld + 8 * lh;
-      const bf16_t* dp = dO + ((size_t)b * S + qc) * d + (size_t)head * DH + 8 * lh;
-      const bf16_t* op = o + ((size_t)b * S + qc) * d + (size_t)head * DH + 8 * lh;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * s));
-        const u32x4 dw = *reinterpret_cast<const u32x4*>(dp + 16 * s), ow = *reinterpret_cast<const u32x4*>(op + 16 * s);
-        dof[s] = __builtin_bit_cast(bf16x8, dw);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          Dq = fmaf(__uint_as_float(dw[e] << 16), __uint_as_float(ow[e] << 16), Dq);
-          Dq = fmaf(__uint_as_float(dw[e] & 0xffff0000u), __uint_as_float(ow[e] & 0xffff0000u), Dq);
-        }
-      }
-    }
-    Dq += __shfl_xor(Dq, 32, 64);
-    const size_t stat = ((size_t)b * h + head) * S + qc;
-    if (lh == 0 && q < S) Dbuf[stat] = Dq;
-    const float nlse2 = -lse[stat] * LOG2E;
-    f32x16 dqacc[CT];
-#pragma unroll
-    for (int c = 0; c < CT; ++c) zero16(dqacc[c]);
-
-    auto ksrc = [&](int kv0) { return [=](int row, int c) { return base + (size_t)min(kv0 + row, S - 1) * ld + d + c * 8; }; };
-    auto vsrc = [&](int kv0) { return [=](int row, int c) { return base + (size_t)min(kv0 + row, S - 1) * ld + 2 * d + c * 8; }; };
-    auto issue_all = [&](u32x4* stage, int kv0) {
-      Stage<64, CPRK, NW>::issue(stage, wave, lane, ksrc(kv0));
-      Stage<64, CPRK, NW>::issue(stage + K_CH, wave, lane, vsrc(kv0));
-    };
-    issue_all(lds, 0);
-    stage_sync();
-
-    for (int j = 0; j < n_tiles; ++j) {
-      const u32x4* ktile = lds + (j & 1) * ST_CH;
-      const u32x4* vtile = ktile + K_CH;
-      u32x4* nxt = lds + ((j + 1) & 1) * ST_CH;
-      const int kv0 = j * 64, kvn = min(j + 1, n_tiles - 1) * 64;
-      issue_all(nxt, kvn);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        const int kg0 = kv0 + 32 * mt;
-        if (kg0 > qw0 + 31) continue;          // wave-uniform: every key of the group lies beyond every query of this wave
-        f32x16 sacc, dpacc;
-        zero16(sacc); zero16(dpacc);
-        {
-          __builtin_amdgcn_sched_barrier(0);
-          bf16x8 kb[2], vb[2];
-          kb[0] = frag<CPRK>(ktile, mt * 32 + l32, lh); vb[0] = frag<CPRK>(vtile, mt * 32 + l32, lh);
-#pragma unroll
-          for (int s = 0; s < KS; ++s) {
-            PP_STEP_BEGIN();
-            if (s + 1 < KS) {
-              kb[(s + 1) & 1] = frag<CPRK>(ktile, mt * 32 + l32, 2 * (s + 1) + lh);
-              vb[(s + 1) & 1] = frag<CPRK>(vtile, mt * 32 + l32, 2 * (s + 1) + lh);
-            }
-            sacc = MFMA(kb[s & 1], qf[s], sacc);
-            dpacc = MFMA(vb[s & 1], dof[s], dpacc);
-            PP_READS_THEN_MFMAS(2, 2);
-          }
-        }
-        if (kg0 + 31 > qw0) {          // wave-uniform: the group straddles the diagonal
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = kg0 + 8 * (r >> 2) + 4 * lh + (r & 3);
-            const float p = key > q ? 0.f : fast_exp2(fmaf(sacc[r], sc2, nlse2));
-            sacc[r] = p * (dpacc[r] - Dq);
-          }
-        } else {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sacc[r] = fast_exp2(fmaf(sacc[r], sc2, nlse2)) * (dpacc[r] - Dq);
-        }
-        bf16x8 dsf[2];
-        dsf[0] = pack8(sacc, 0); dsf[1] = pack8(sacc, 8);
-        {
-          __builtin_amdgcn_sched_barrier(0);
-          bf16x8 tb[2];          // K^T block n % CT for the 16 keys 32 mt + 16 (n / CT) ..
-          const uint32_t ktl = launder(lds_byte_offset(ktile) + tr_off);
-          tb[0] = frag_tr<CPRK>(ktl, 32 * mt, 0);
-          tb[1] = frag_tr<CPRK>(ktl, 32 * mt + 16 * (1 / CT), 1 % CT);
-#pragma unroll
-          for (int sp = 0; sp < CT; ++sp) {          // two (u, c) steps per fence
-            PP_STEP_BEGIN();
-            bf16x8 cur0 = tb[0], cur1 = tb[1];
-            if (sp + 1 < CT) {
-              const int n0 = 2 * sp + 2, n1 = 2 * sp + 3;
-              const uint32_t kt2 = launder(ktl);
-              tb[0] = frag_tr<CPRK>(kt2, 32 * mt + 16 * (n0 / CT), n0 % CT);
-              tb[1] = frag_tr<CPRK>(kt2, 32 * mt + 16 * (n1 / CT), n1 % CT);
-            }
-            const int a0 = 2 * sp, a1 = 2 * sp + 1;
-            dqacc[a0 % CT] = MFMA(cur0, dsf[a0 / CT], dqacc[a0 % CT]);
-            dqacc[a1 % CT] = MFMA(cur1, dsf[a1 / CT], dqacc[a1 % CT]);
-            PP_READS_THEN_MFMAS(4, 2);
-          }
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      stage_sync();
-    }
-    if (q < S) {
-      unrotate_tile<DH>(dqacc, cosb, sinb, q, lh);          // dQ w.r.t. the un-rotated query (linear: commutes with the scale below)
-      bf16_t* op = dqkv + ((size_t)b * S + q) * ld + (size_t)head * DH + 4 * lh;
-#pragma unroll
-      for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          u32x2 w;
-          w[0] = pack_bf16x2(dqacc[c][4 * g] * scale, dqacc[c][4 * g + 1] * scale);
-          w[1] = pack_bf16x2(dqacc[c][4 * g + 2] * scale, dqacc[c][4 * g + 3] * scale);
-          *reinterpret_cast<u32x2*>(op + c * 32 + 8 * g) = w;
-        }
-    }
+    attn_bwd_dq_block<DH, NW, false>(lds, qkv, o, dO, lse, Dbuf, dqkv, S, h, pair % h, pair / h, qblk, lane, wave, cosb, sinb);
   }
 }
 
@@ -706,6 +721,42 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkv_kernel(const bf16_t* __re
   }
 }
 
+// ------------------------------------------------------------------------------------------ backward in one launch
+// D = rowsum(dO * O): two lanes per row and head, each every second 8-element piece; the sums of the dQ kernel in its order.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_bwd_d_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ dO, float* __restrict__ Dbuf, int S, int h, int n) {
+  const int t = blockIdx.x * 256 + threadIdx.x, i = min(t >> 1, n - 1);          // i = (b S + q) h + head
+  const bf16_t* op = o + (size_t)i * DH + 8 * (t & 1);
+  const bf16_t* dp = dO + (size_t)i * DH + 8 * (t & 1);
+  float D = 0.f;
+#pragma unroll
+  for (int s = 0; s < DH / 16; ++s) D = d_piece(*reinterpret_cast<const u32x4*>(dp + 16 * s), *reinterpret_cast<const u32x4*>(op + 16 * s), D);
+  D += __shfl_xor(D, 1, 64);
+  const int head = i % h, row = i / h;
+  if ((t & 1) == 0 && (t >> 1) < n) Dbuf[((size_t)(row / S) * h + head) * S + row % S] = D;
+}
+
+// dK/dV blocks of 128 keys and dQ blocks of 256 queries in one grid, heaviest first.  Where neither fills the chip for a round each of the two kernels lasts
+// as long as its longest block (the chain over all of a sequence's tiles) with half the chip idle towards its end; together they last hardly longer than one.
+// Groups of three workgroups per pair: dK/dV blocks 2 g and 2 g + 1 and the dQ block of the same number of tiles.
+template <int DH>
+__global__ __launch_bounds__(512, 2) void attn_bwd_both_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ dO,
+                                                               const float* __restrict__ lse, float* __restrict__ Dbuf, bf16_t* __restrict__ dqkv, int S, int h, int n_pairs,
+                                                               int nb_kv, int nb_dq, const float* __restrict__ cosb, const float* __restrict__ sinb) {
+  extern __shared__ u32x4 lds[];
+  const int g = blockIdx.x / (3 * n_pairs), x = blockIdx.x - g * 3 * n_pairs, kind = x / n_pairs, pair = x - kind * n_pairs;
+  const int head = pair % h, b = pair / h;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (kind == 1) {
+    attn_bwd_dq_block<DH, 8, true>(lds, qkv, o, dO, lse, Dbuf, dqkv, S, h, head, b, nb_dq - 1 - g, lane, wave, cosb, sinb);
+    return;
+  }
+  const int kblk = 2 * g + (kind >> 1);
+  if (kblk >= nb_kv) return;          // an odd number of blocks of 128
+  if (wave >= 4) attn_bwd_dkv_part<DH, true>(lds, qkv, dO, lse, Dbuf, dqkv, S, h, head, b, kblk, lane, wave, cosb, sinb);
+  else attn_bwd_dkv_part<DH, false>(lds, qkv, dO, lse, Dbuf, dqkv, S, h, head, b, kblk, lane, wave, cosb, sinb);
+}
+
 // ------------------------------------------------------------------------------------------ host side
 template <class K>
 static bool set_lds(K kern, int bytes) {
@@ -719,6 +770,13 @@ static bool set_lds(K kern, int bytes) {
 // paired workgroups on 512 and 256 slots) 33.4 + 98.5 / 27.6 + 83.8; 8 x 1000, 20 heads of 128 79.5 + 255 / 70.1 + 239; 8 x 512, 24 heads of 64 23.4 + 69.5 /
 // 20.7 + 60.1.
 static int full_rounds(long wgs, long slots) { return 5 * wgs >= 4 * slots * ((wgs + slots - 1) / slots); }
+
+// dQ and dK/dV in one grid (wgs workgroups of eight waves, nb_kv blocks of 128 keys per sequence): wherever all of it is resident at once (one workgroup per
+// unit), and beyond that while long sequences leave most of the blocks short.  us, two kernels / one with the D kernel in front of it: 3 x 777, 12 heads of 64 (396
+// workgroups, 7 blocks) 40.3 / 34.1; 1 x 200, 4 heads of 64 18.1 / 13.1; 1 x 2048, 8 heads of 64 82 / 50; 1 x 2048, 16 heads of 128 (384, 16) 122 / 85; 5 x 611, 12 heads of 64 (480,
+// 5) 36.0 / 33.6; 24 heads of 2154 x 64 (624, 17) 101 / 86; against it 66 of 579 x 64 (528, 5) 38.6 / 39.8; 96 of 260 x 128 (480, 3) 34.2 / 38.8; 75 of 365 x 64 (375, 3) 25.7 / 26.5; 60
+// of 2100 x 128 (1560, 17) 303 / 335.
+static bool one_launch(long wgs, long nb_kv) { return wgs <= 256 || (wgs <= 96 * nb_kv && wgs <= 768); }
 
 template <int DH>
 static int fwd_launch(hipStream_t st, const void* qkv, void* o, float* lse, int B, int S, int h) {
@@ -739,10 +797,17 @@ static int bwd_launch(hipStream_t st, const void* qkv, const void* o, const floa
   constexpr int DQ_LDS = 2 * (2 * 64 * (DH / 8)) * 16;                                   // two stages of K rows + V rows
   constexpr int DKV_LDS = (3 * (2 * 64 * (DH / 8)) + 2 * (2 * 4 * 2 * 64) + 3 * 32) * 16;          // three sets of Q rows + dO rows, two P mailboxes, three sets of statistics
   static bool ok = set_lds(attn_bwd_dq_kernel<DH, 4>, DQ_LDS) && (DH == 64 || set_lds(attn_bwd_dq_kernel<128, 8>, DQ_LDS)) &&
-                   set_lds(attn_bwd_dkv_kernel<DH, true>, DKV_LDS) && set_lds(attn_bwd_dkv_kernel<DH, false>, DKV_LDS);
+                   set_lds(attn_bwd_dkv_kernel<DH, true>, DKV_LDS) && set_lds(attn_bwd_dkv_kernel<DH, false>, DKV_LDS) && set_lds(attn_bwd_both_kernel<DH>, DKV_LDS);
   if (!ok) return 1;
   const int nb_kv = (S + 127) / 128, nb_dq = (S + 255) / 256;
   const long paired_dq = (long)B * h * ((nb_dq + 1) / 2), paired_kv = (long)B * h * ((nb_kv + 1) / 2);
+  if (one_launch((long)B * h * (nb_kv + nb_dq), nb_kv) && (long)B * S * h < (1l << 30)) {
+    const int n = B * S * h;
+    attn_bwd_d_kernel<DH><<<dim3((unsigned)((2l * n + 255) / 256)), 256, 0, st>>>((const bf16_t*)o, (const bf16_t*)dO, Dbuf, S, h, n);
+    attn_bwd_both_kernel<DH><<<dim3((unsigned)(3 * B * h * nb_dq)), 512, DKV_LDS, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, Dbuf, (bf16_t*)dqkv, S, h, B * h, nb_kv, nb_dq,
+                                                                                       cosb, sinb);
+    return 0;
+  }
   // the dQ kernel also writes D = rowsum(dO * O), which the dK/dV kernel then reads.
   // Single blocks of 128 queries fill every grid best but some at head dim 128 with 1024 positions and more, where equal workgroups that
   // fill the chip once, or three times and more, lose nothing to a last round and read K and V half as often.  us, paired 256 / single 128,
