@@ -180,7 +180,8 @@ int pp_get_launch_counts(pp_model* m, int64_t* matrix_core_calls, int64_t* plain
  * units, one workgroup per unit walks several tiles and requests its next tile's first operands before the current
  * tile's epilogue; 0 = one workgroup per tile.  Same results bit for bit.
  * "gemm_small_tiles" (process-wide, same caveats; m may be NULL): 1 (default) = GEMMs with at most 128 output tiles of
- * 256 x 256 (half a tile per compute unit) run on smaller tiles, 64 x 64 to 256 x 128; 0 = always 256 x 256 tiles. */
+ * 256 x 256 (half a tile per compute unit) run on smaller tiles, 32 x 64 to 128 x 256, and the SwiGLU and rotary GEMMs on 128 x 192 tiles
+ * where that is faster; 0 = always 256 x 256 tiles.  Same results bit for bit. */
 int pp_set_option(pp_model* m, const char* key, int64_t value);
 
 /* Blocks until the stream is idle, then returns the summed duration (ms), matmul FLOPs and number of the GEMM

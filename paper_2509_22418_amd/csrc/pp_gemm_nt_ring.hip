@@ -38,9 +38,16 @@ template <int N> __device__ __forceinline__ void wait_vm_lgkm0() {          // v
 // memory pipeline's queue (16 cycles a load, 40 loads a step at 128 x 192) ahead of their own MFMAs, and the compiler waited for the reads of the NEXT half
 // step in front of the current one's MFMAs.  us, before / now: 8192 x 768, K = 32000 408 / 361; 2048 x 2048, K = 2048 21.9 / 17.0 (128 x 128); 3055 x 768, K = 3072 25.6 /
 // 21.0 (64 x 96 / 128 x 128); 1003 x 768, K = 768 6.2 / 5.3 (64 x 64); 500 x 2048, K = 8192 40.6 / 27.0 (64 x 64, three / four stages).
+struct RingFused {          // operands of the fused epilogues (ring_fused below)
+  int half;                 // SWIGLU: d_ff; SWIGLU_BWD: columns from a gate to its up; ROPE: half a head
+  int rot;                  // ROPE: leading columns that are rotated (q and k)
+  int seq;                  // ROPE: sequence length
+  bf16_t* act;              // SWIGLU: silu(gate) * up [M x d_ff]
+  const float *cosb, *sinb; // ROPE: [seq x half]
+};
 template <int EPI, int BM, int BN, int WM, int WN, int NS, bool WHOLE, bool TOUCH>
-__global__ __launch_bounds__(64 * WM * WN, WHOLE ? 1 : 2) void gemm_nt_ring_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
-                                                                         bf16_t* C, int ldc, int M, int N, int K, const bf16_t* R, int tiles_m, int tiles_n, int vec, int touch) {
+__global__ __launch_bounds__(64 * WM * WN, WHOLE ? 1 : NS == 2 ? 4 : 2) void gemm_nt_ring_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
+                                                                         bf16_t* C, int ldc, int M, int N, int K, const bf16_t* R, int tiles_m, int tiles_n, int vec, int touch, RingFused fu) {
   constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, MI = TM / 16, NJ = TN / 16, FR = MI + NJ;
   constexpr int STAGE = (BM + BN) * 128, LPW = (BM + BN) / 8 / NW;          // bytes of a stage; wave-loads (8 rows) per wave
   constexpr int PITCH = TN * 4 + 16;                                         // epilogue patch: bytes per row
@@ -65,7 +72,14 @@ __global__ __launch_bounds__(64 * WM * WN, WHOLE ? 1 : 2) void gemm_nt_ring_kern
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
     const int row = (wave + NW * i) * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
-    g[i] = row < BM ? A + (size_t)min(m0 + row, M - 1) * lda + c * 8 : B + (size_t)min(n0 + row - BM, N - 1) * ldb + c * 8;
+    int brow = min(n0 + row - BM, N - 1);
+    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ROPE) {
+      // A wave's TN columns are TN / 2 first members and their partners: gate and up of the same hidden units, or the two halves of rotary pairs
+      const int br = row - BM, w = br / TN, q = br % TN, pr = n0 / 2 + w * (TN / 2) + q % (TN / 2), second = q / (TN / 2);
+      if constexpr (EPI == EPI_SWIGLU) brow = second * N + min(pr, N - 1);
+      else if (n0 < fu.rot) brow = pr / fu.half * 2 * fu.half + pr % fu.half + second * fu.half;
+    }
+    g[i] = row < BM ? A + (size_t)min(m0 + row, M - 1) * lda + c * 8 : B + (size_t)brow * ldb + c * 8;
   }
   auto load1 = [&](int i, int s, int slot) {          // wave-load i of stage s
     __builtin_amdgcn_global_load_lds(PP_R_GPTR(g[i] + (size_t)s * 64), PP_R_LPTR(r_lds + slot * STAGE + wave * 1024 + i * NW * 1024), 16, 0, 0);
@@ -202,11 +216,56 @@ __global__ __launch_bounds__(64 * WM * WN, WHOLE ? 1 : 2) void gemm_nt_ring_kern
   static_assert(32 * PR % 64 == 0, "pieces");
 #pragma unroll
   for (int p = 0; p < MI / 2; ++p) {
+    [[maybe_unused]] uint4 gate[NP], up[NP];          // SWIGLU_BWD: requested ahead of the patch's round trip, from clamped addresses
+    if constexpr (EPI == EPI_SWIGLU_BWD) {
+#pragma unroll
+      for (int it = 0; it < NP; ++it) {
+        const int idx = it * 64 + lane;
+        const bf16_t* r = R + (size_t)min(m0 + wm * TM + p * 32 + idx / PR, M - 1) * ldc + min(n0 + wn * TN + idx % PR * 8, N - 8);
+        gate[it] = *reinterpret_cast<const uint4*>(r);
+        up[it] = *reinterpret_cast<const uint4*>(r + fu.half);
+      }
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
         *reinterpret_cast<float4*>(patch + (i * 16 + l16) * PITCH + j * 64 + lq * 16) = make_float4(acc[2 * p + i][j][0], acc[2 * p + i][j][1], acc[2 * p + i][j][2], acc[2 * p + i][j][3]);
+    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ROPE) {
+      if (EPI == EPI_SWIGLU || n0 < fu.rot) {          // pairs: 8 first members and their partners TN / 2 columns further on
+        constexpr int HP = TN / 16;
+#pragma unroll
+        for (int it = 0; it < (32 * HP + 63) / 64; ++it) {
+          const int idx = it * 64 + lane, row = idx / HP, c = idx % HP;
+          const int grow = m0 + wm * TM + p * 32 + row, pr = n0 / 2 + wn * (TN / 2) + c * 8;
+          if (idx >= 32 * HP || grow >= M) continue;
+          float x[8], y[8];
+          load8(reinterpret_cast<const float*>(patch + row * PITCH + c * 32), x);
+          load8(reinterpret_cast<const float*>(patch + row * PITCH + TN * 2 + c * 32), y);
+          bf16_t* out = C + (size_t)grow * ldc;
+          if constexpr (EPI == EPI_SWIGLU) {
+            if (pr >= N) continue;
+            store8(out + pr, x);
+            store8(out + N + pr, y);
+            float a[8];          // from the rounded values, as a pass over the stored matrix would form it
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a[e] = silu_mul(bf16_to_f32(f32_to_bf16(x[e])), bf16_to_f32(f32_to_bf16(y[e])));
+            store8(fu.act + (size_t)grow * N + pr, a);
+          } else {
+            const int head = pr / fu.half, i = pr - head * fu.half;
+            const size_t at = (size_t)(grow % fu.seq) * fu.half + i;
+            float cs[8], sn[8], a[8], b[8];
+            load8(fu.cosb + at, cs);
+            load8(fu.sinb + at, sn);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { a[e] = fmaf(x[e], cs[e], -(y[e] * sn[e])); b[e] = fmaf(y[e], cs[e], x[e] * sn[e]); }          // as the big-tile kernel rounds them
+            store8(out + head * 2 * fu.half + i, a);
+            store8(out + head * 2 * fu.half + i + fu.half, b);
+          }
+        }
+        continue;
+      }
+    }
     auto store = [&](auto V) {          // V consecutive columns exist as a whole and are aligned
       constexpr int VEC = decltype(V)::value;
 #pragma unroll
@@ -218,7 +277,20 @@ __global__ __launch_bounds__(64 * WM * WN, WHOLE ? 1 : 2) void gemm_nt_ring_kern
         if (grow >= M || gcol >= N) continue;
         float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
         const size_t off = (size_t)grow * ldc + gcol;
-        if constexpr (VEC == 8) {
+        if constexpr (VEC == 8 && EPI == EPI_SWIGLU_BWD) {          // the product is dL/da: dg and du go to the places of gate and up
+          float dg[8], du[8];
+          const uint32_t gw[4] = {gate[it].x, gate[it].y, gate[it].z, gate[it].w}, uw[4] = {up[it].x, up[it].y, up[it].z, up[it].w};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float gg = (e & 1) ? __uint_as_float(gw[e >> 1] & 0xffff0000u) : __uint_as_float(gw[e >> 1] << 16);
+            const float uu = (e & 1) ? __uint_as_float(uw[e >> 1] & 0xffff0000u) : __uint_as_float(uw[e >> 1] << 16);
+            const float sg = sigmoid_fast(gg);
+            du[e] = v[e] * gg * sg;
+            dg[e] = v[e] * uu * sg * (1.0f + gg * (1.0f - sg));
+          }
+          store8(C + off, dg);
+          store8(C + off + fu.half, du);
+        } else if constexpr (VEC == 8) {
           if constexpr (EPI == EPI_ADD_RES) {
             float r[8];
             load8(R + off, r);
@@ -245,7 +317,8 @@ __global__ __launch_bounds__(64 * WM * WN, WHOLE ? 1 : 2) void gemm_nt_ring_kern
         }
       }
     };
-    if (vec == 8) store(std::integral_constant<int, 8>{});
+    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_BWD || EPI == EPI_ROPE) store(std::integral_constant<int, 8>{});          // whole aligned groups of 8 only
+    else if (vec == 8) store(std::integral_constant<int, 8>{});
     else if (vec == 4) store(std::integral_constant<int, 4>{});
     else store(std::integral_constant<int, 1>{});
   }
@@ -263,7 +336,7 @@ static int launch_ring(hipStream_t st, const void* A, int lda, const void* B, in
   const int vec = ((N | ldc) & 7) == 0 && (al & 15) == 0 ? 8 : ((N | ldc) & 3) == 0 && (al & 7) == 0 ? 4 : 1;
   const long threads = (long)tiles_m * tiles_n * 64 * WM * WN, pieces = (long)N * (K / 64);
   const int touch = TOUCH ? (int)std::min(4l, (pieces + threads - 1) / threads) : 0;          // words of B per thread
-  kern<<<dim3(tiles_m * tiles_n), 64 * WM * WN, LDS, st>>>((const bf16_t*)A, lda, (const bf16_t*)B, ldb, (bf16_t*)C, ldc, M, N, K, (const bf16_t*)R, tiles_m, tiles_n, vec, touch);
+  kern<<<dim3(tiles_m * tiles_n), 64 * WM * WN, LDS, st>>>((const bf16_t*)A, lda, (const bf16_t*)B, ldb, (bf16_t*)C, ldc, M, N, K, (const bf16_t*)R, tiles_m, tiles_n, vec, touch, RingFused{});
   return 0;
 }
 // The tiles, with what was measured of each (ns): one K step of 64 when 1, 2, .. workgroups share a compute unit and every unit has one; the part of
@@ -318,6 +391,29 @@ static int dispatch_ring(hipStream_t st, const void* A, int lda, const void* B, 
     case 6: return launch_half<EPI, 128, 192, 3>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
     default: return launch_half<EPI, 128, 256, 3>(st, A, lda, B, ldb, C, ldc, M, N, K, R);
   }
+}
+
+// The SwiGLU and rotary GEMMs on 128 x 192 tiles, two stages, two workgroups per unit (80 KB, 128 registers a wave): the bytes of one's epilogue move behind the other's
+// MFMAs.  The same bits as the big-tile kernel's.
+template <int EPI>
+static int launch_fused(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const void* R, int tiles_n, const RingFused& fu) {
+  constexpr int LDS = 2 * (128 + 192) * 128;
+  auto kern = gemm_nt_ring_kernel<EPI, 128, 192, 2, 4, 2, false, false>;
+  static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS) == hipSuccess;
+  if (!ok) return 1;
+  const int tiles_m = (M + 127) / 128;
+  kern<<<dim3(tiles_m * tiles_n), 512, LDS, st>>>((const bf16_t*)A, lda, (const bf16_t*)B, ldb, (bf16_t*)C, ldc, M, N, K, (const bf16_t*)R, tiles_m, tiles_n, 8, 0, fu);
+  return 0;
+}
+int k_gemm_swiglu_fwd_ring(hipStream_t st, const void* X, int ldx, const void* Wgu, int ldw, void* gu, void* a, int M, int F, int K) {
+  return launch_fused<EPI_SWIGLU>(st, X, ldx, Wgu, ldw, gu, 2 * F, M, F, K, nullptr, (F + 95) / 96, RingFused{F, 0, 0, (bf16_t*)a, nullptr, nullptr});
+}
+int k_gemm_swiglu_bwd_ring(hipStream_t st, const void* G, int ldg, const void* Wd_rows, int ldw, const void* gu_c0, void* dgu_c0, int ld2f, int half, int M, int N, int K) {
+  return launch_fused<EPI_SWIGLU_BWD>(st, G, ldg, Wd_rows, ldw, dgu_c0, ld2f, M, N, K, gu_c0, (N + 191) / 192, RingFused{half, 0, 0, nullptr, nullptr, nullptr});
+}
+int k_gemm_qkv_rope_ring(hipStream_t st, const void* X, int ldx, const void* Wqkv, int ldw, void* qkv, int M, int d, int dh, int K, int S, const float* rope_cos, const float* rope_sin) {
+  if (d % 192) return 1;          // a tile is all rotated pairs or none, and no row block is cut
+  return launch_fused<EPI_ROPE>(st, X, ldx, Wqkv, ldw, qkv, 3 * d, M, 3 * d, K, nullptr, 3 * d / 192, RingFused{dh / 2, 2 * d, S, nullptr, rope_cos, rope_sin});
 }
 
 // bf16 output, epi = EPI_STORE or EPI_ADD_RES (R with leading dimension ldc).  Returns 0 if launched, 1 if the shape is not

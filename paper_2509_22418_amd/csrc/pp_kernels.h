@@ -105,6 +105,10 @@ int k_gemm_tn_mfma(hipStream_t st, const void* A, int lda, int m_blk, long a_blk
                    int M, int N, int K, int kchunk, float* partial, int sub = 0x40000000);          // sub: rows per running fp32 sum (a multiple of 64)
 // smaller tiles (32 x 64 to 128 x 256, chosen by shape) for shapes with too few 256 x 256 tiles to fill the chip (bf16 out, EPI_STORE / EPI_ADD_RES)
 int k_gemm_nt_ring(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, int epi, const void* R);
+// the fused GEMMs on the same tiles; arguments as, and checked by, k_gemm_swiglu_fwd_mfma, k_gemm_swiglu_bwd_mfma and k_gemm_qkv_rope_mfma
+int k_gemm_swiglu_fwd_ring(hipStream_t st, const void* X, int ldx, const void* Wgu, int ldw, void* gu, void* a, int M, int F, int K);
+int k_gemm_swiglu_bwd_ring(hipStream_t st, const void* G, int ldg, const void* Wd_rows, int ldw, const void* gu_c0, void* dgu_c0, int ld2f, int half, int M, int N, int K);
+int k_gemm_qkv_rope_ring(hipStream_t st, const void* X, int ldx, const void* Wqkv, int ldw, void* qkv, int M, int d, int dh, int K, int S, const float* rope_cos, const float* rope_sin);
 void gemm_set_small_tiles(int v);      // 1 (default): k_gemm_nt_mfma hands GEMMs with at most 128 tiles of 256 x 256 (half a tile per compute unit) to k_gemm_nt_ring
 void gemm_set_variant(int v);          // 0: register-staged MFMA GEMM, 1: direct-to-LDS MFMA GEMM
 void gemm_set_persistent(int v);       // 1 (default): a workgroup per compute unit walks several tiles when there are more tiles than units
