@@ -165,11 +165,11 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const T* __restrict__
 
 // ------------------------------------------------------------------------------------------ backward: dQ
 template <int DH, class T>
-__global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
-                                                              const T* __restrict__ dO, T* __restrict__ dqkv, int S, int h, int n_pairs) {
-  __shared__ float ds[32 * BPITCH], Ls[32], Ds[32];
+__device__ __forceinline__ void attn_bwd_dq_f32(float* ds, const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
+                                                const T* __restrict__ dO, T* __restrict__ dqkv, int S, int h, int pair, int rank) {
+  float *Ls = ds + 32 * BPITCH, *Ds = Ls + 32;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lh = lane >> 5, l16 = lane & 15, lg = lane >> 4;
-  const int pair = blockIdx.x % n_pairs, qb = (S + 31) / 32 - 1 - blockIdx.x / n_pairs;
+  const int qb = (S + 31) / 32 - 1 - rank;
   const int head = pair % h, b = pair / h, q0 = qb * 32, nk = min(S, q0 + 32);
   const int d = h * DH;
   const size_t ld = (size_t)3 * d;
@@ -231,11 +231,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(const T* __restric
 
 // ------------------------------------------------------------------------------------------ backward: dK, dV
 template <int DH, class T>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
-                                                               const T* __restrict__ dO, T* __restrict__ dqkv, int S, int h, int n_pairs) {
-  __shared__ float Pt[32 * BPITCH], DSt[32 * BPITCH];          // [key][query of the chunk]
+__device__ __forceinline__ void attn_bwd_dkv_f32(float* Pt, const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
+                                                 const T* __restrict__ dO, T* __restrict__ dqkv, int S, int h, int pair, int kb) {
+  float* DSt = Pt + 32 * BPITCH;          // [key][query of the chunk], both
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lh = lane >> 5, l16 = lane & 15, lg = lane >> 4;
-  const int pair = blockIdx.x % n_pairs, kb = blockIdx.x / n_pairs;          // early keys see the most queries
   const int head = pair % h, b = pair / h, k0 = kb * 32;
   const int d = h * DH;
   const size_t ld = (size_t)3 * d;
@@ -303,6 +302,32 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(const T* __restri
   }
 }
 
+// ------------------------------------------------------------------------------------------ backward: both in one grid, heaviest blocks first (early keys see the most
+// queries, late queries the most keys).  They share nothing but D, and together they leave fewer units idle behind the longest blocks.  us, two launches / one: 4 x 256, 8 heads of
+// 64 47.5 / 36.9, 1 x 256, 8 heads of 64 46.7 / 27.9, 2 x 1000, 4 heads of 64 140 / 103, 8 x 320, 12 heads of 64 123 / 119, 4 x 128, 16 heads of 32 21 / 15.  At head dim 128 one kernel for both
+// has the registers of the larger: 16 pairs of 600 (304 blocks of 32 rows) 202 / 173, but 16 of 1000 (512) 370 / 404, 128 of 300 (1280) 417 / 437.
+constexpr unsigned kOneGrid128 = 400;          // blocks of 32 rows
+template <int DH, class T, bool DQ, bool DKV>
+__global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
+                                                           const T* __restrict__ dO, T* __restrict__ dqkv, int S, int h, int n_pairs) {
+  __shared__ float lds[2 * 32 * BPITCH];
+  static_assert(32 * BPITCH >= 64, "room for the statistics of 32 rows");
+  constexpr int KINDS = DQ + DKV;
+  const int rank = blockIdx.x / (KINDS * n_pairs), x = blockIdx.x - rank * KINDS * n_pairs;
+  if (DKV && x < n_pairs) attn_bwd_dkv_f32<DH>(lds, qkv, lse, Dbuf, dO, dqkv, S, h, x, rank);
+  else if (DQ) attn_bwd_dq_f32<DH>(lds, qkv, lse, Dbuf, dO, dqkv, S, h, DKV ? x - n_pairs : x, rank);
+}
+template <int DH, class T>
+static void bwd_f32(hipStream_t st, const void* qkv, const float* lse, const float* Dbuf, const void* dO, void* dqkv, int B, int S, int h) {
+  const unsigned blocks = (unsigned)B * h * ((S + 31) / 32);
+  if (DH < 128 || blocks <= kOneGrid128) {
+    attn_bwd_f32_kernel<DH, T, true, true><<<2 * blocks, 256, 0, st>>>((const T*)qkv, lse, Dbuf, (const T*)dO, (T*)dqkv, S, h, B * h);
+  } else if constexpr (DH == 128) {
+    attn_bwd_f32_kernel<DH, T, true, false><<<blocks, 256, 0, st>>>((const T*)qkv, lse, Dbuf, (const T*)dO, (T*)dqkv, S, h, B * h);
+    attn_bwd_f32_kernel<DH, T, false, true><<<blocks, 256, 0, st>>>((const T*)qkv, lse, Dbuf, (const T*)dO, (T*)dqkv, S, h, B * h);
+  }
+}
+
 // ------------------------------------------------------------------------------------------ host side
 static bool shapes_ok(int dtype, const void* a, const void* b, int S, int h, int dh) {
   const uintptr_t al = dtype == 0 ? 15 : 7;          // rows are read four elements at a time
@@ -327,16 +352,12 @@ static int fwd_f32(hipStream_t st, const void* qkv, void* o, float* lse, int B, 
   } while (0)
 
 // Few rows, short rows: the vector kernels run a workgroup per row, all at once up to about 3000 of them, and then last as long as one row;
-// here a workgroup of 32 rows is a chain of three dependent phases.  What pays is pairs x S^2 (pairs = B h), and for the backward, whose
-// vector chain is longer, also the length alone.  The lines below are where both took the same time (pairs 1 .. 128, S 1 .. 1150; fp32, us, vector / these):
-//   forward   dh 16: 16 x 33 5.4 / 8.4, 16 x 80 8.0 / 9.8, 32 x 64 11.0 / 8.8, 4 x 200 13.8 / 14.4, 4 x 256 18.5 / 15.7
-//             dh 32: 64 x 33 7.7 / 8.8, 96 x 32 14.8 / 8.7, 8 x 128 17.2 / 11.8     dh 64: 16 x 48 9.5 / 10.4, 16 x 64 12.7 / 11.2, 64 x 32 11.9 / 10.3
-//   backward  dh 64: 1 x 48 22.7 / 24.7, 1 x 64 28.3 / 25.1, 32 x 32 27.2 / 24.6     dh 128: 4 x 64 43.5 / 45.4, 1 x 128 61.3 / 53.7, 8 x 80 69.2 / 48.1
-static bool fwd_pays(long pairs, int S, int dh) {
-  if (dh == 32 && S >= 32 && pairs * S >= 3072) return true;
-  return pairs * S * S >= (dh >= 64 ? 1 << 16 : dh == 16 && pairs < 8 ? 1 << 18 : 1 << 17);
-}
-static bool bwd_pays(long pairs, int S, int dh) { return dh == 128 ? S >= 128 || pairs * S * S >= 40000 : S >= 64 || pairs * S * S >= 1 << 15; }
+// here a workgroup of 32 rows is a chain of three dependent phases.  For the forward the number of rows is what counts, for the backward, whose vector chain is
+// longer, pairs x S^2 (pairs = B h).  The lines below are where both took the same time (pairs 1 .. 96, S 33 .. 256; fp32, us, vector / these):
+//   forward   dh 16: 64 x 64 8.2 / 8.9, 96 x 64 11.0 / 9.0      dh 64: 16 x 160 16.1 / 17.9, 16 x 256 32 / 21      dh 128: 4 x 256 23.6 / 30.3, 64 x 48 13.4 / 14.8, 64 x 64 22 / 16
+//   backward  dh 16: 4 x 48 7.9 / 8.2, 16 x 33 8.2 / 8.0     dh 32: 16 x 48 9.2 / 10.5, 4 x 160 19.1 / 15.4     dh 64: 16 x 64 14.6 / 16.1, 4 x 160 25.3 / 24.3     dh 128: 4 x 160 38.6 / 46.8, 64 x 48 43.4 / 28.8
+static bool fwd_pays(long pairs, int S, int dh) { return pairs * S >= (dh == 16 ? 4608 : 3444); }
+static bool bwd_pays(long pairs, int S, int dh) { return pairs * S * S >= (dh == 16 ? 10000 : dh == 32 ? 46000 : dh == 64 ? 78000 : 110000); }
 // The scores of 32 queries against the whole sequence sit in LDS: sequences of more than MAX_S positions return 1.
 int k_attn_fwd_f32(hipStream_t st, int dtype, const void* qkv, void* o, float* lse, int B, int S, int h, int dh) {
   if (S > MAX_S || !shapes_ok(dtype, qkv, o, S, h, dh) || !fwd_pays((long)B * h, S, dh)) return 1;
@@ -348,9 +369,7 @@ int k_attn_fwd_f32(hipStream_t st, int dtype, const void* qkv, void* o, float* l
 int k_attn_bwd_f32(hipStream_t st, int dtype, const void* qkv, const void* o, const float* lse, const void* dO, void* dqkv, float* Dbuf, int B, int S, int h, int dh) {
   if (!shapes_ok(dtype, qkv, dO, S, h, dh) || !bwd_pays((long)B * h, S, dh)) return 1;
   k_attn_D(st, dtype, o, dO, Dbuf, B, S, h, dh);
-  const unsigned grid = (unsigned)B * h * ((S + 31) / 32);
-  PP_F32_ATTN(dtype, dh, (attn_bwd_dq_f32_kernel<DH, T><<<grid, 256, 0, st>>>((const T*)qkv, lse, Dbuf, (const T*)dO, (T*)dqkv, S, h, B * h)));
-  PP_F32_ATTN(dtype, dh, (attn_bwd_dkv_f32_kernel<DH, T><<<grid, 256, 0, st>>>((const T*)qkv, lse, Dbuf, (const T*)dO, (T*)dqkv, S, h, B * h)));
+  PP_F32_ATTN(dtype, dh, (bwd_f32<DH, T>(st, qkv, lse, Dbuf, dO, dqkv, B, S, h)));
   return 0;
 }
 
