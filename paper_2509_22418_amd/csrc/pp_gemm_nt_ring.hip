@@ -34,7 +34,7 @@ template <int N> __device__ __forceinline__ void wait_vm_lgkm0() {          // v
 //   true: all fragments of step s + 1 are read while step s is multiplied (two whole sets of registers).  One wait and one barrier per step with the
 //     whole step's MFMAs between a read and its use: what a tile needs whose MFMAs alone are shorter than two trips to LDS (64 x 64: 8 per wave).
 //   false: half a step (32 of K) ahead, half the registers, so that 64 x 48 and 64 x 64 per wave fit without spilling.
-// In both forms every fragment read and every load stands behind an MFMA of its own (Items).  With a step's loads issued in one go the waves sat in the
+// In both forms every fragment read and every load stands behind an MFMA of its own.  With a step's loads issued in one go the waves sat in the
 // memory pipeline's queue (16 cycles a load, 40 loads a step at 128 x 192) ahead of their own MFMAs, and the compiler waited for the reads of the NEXT half
 // step in front of the current one's MFMAs.  us, before / now: 8192 x 768, K = 32000 408 / 361; 2048 x 2048, K = 2048 21.9 / 17.0 (128 x 128); 3055 x 768, K = 3072 25.6 /
 // 21.0 (64 x 96 / 128 x 128); 1003 x 768, K = 768 6.2 / 5.3 (64 x 64); 500 x 2048, K = 8192 40.6 / 27.0 (64 x 64, three / four stages).
