@@ -505,35 +505,10 @@ extern "C" int pp_set_trainable_mask(pp_model* m, const pp_mask* mask, void* sta
 }
 
 // ------------------------------------------------------------------------------------------------ GEMM dispatch
-// K ranges for a product of few tiles and a contraction over the vocabulary (the gradient of the final norm's output): whatever the tile, one
-// round of small tiles walks all of K with part of the chip idle, so the 256 x 256 tiles of several ranges go side by side and a second kernel adds their
-// fp32 sums (shorter chains than the one over all of K) and rounds once.  Taken where both estimates say that it saves a sixth.  3055 x 768, K = 32000: 265 us in one
-// range, 150 in five with the sum.  0 = one range.
-static int vocab_ranges(const pp_model* m, int M, int N, int K) {
-  if (K % 64 || K < 16384) return 0;
-  const long tiles = ((M + 255l) / 256) * ((N + 255l) / 256), out = (long)M * N;
-  if (tiles > 64) return 0;
-  int n = 0;
-  for (int s = 2; s <= 32 && tiles * s <= 256 && out * 4 * s <= (long)m->ws.partial_bytes; ++s)
-    if (K / 64 % s == 0 && K / s >= 1024) n = s;
-  if (n < 2) return 0;
-  const long ns = K / n / 64 * 1450 + 8000 + out * (4 * n + 2) / 4000;
-  const long one = k_gemm_nt_ring_ns(M, N, K) * ((long)M * K * 2 > (64l << 20) ? 4 : 3) / 3;          // its figures are of an A in cache: a third more for one that streams (197 estimated, 269 measured)
-  return 6 * ns < 5 * one ? n : 0;
-}
 static void gemm_nt(pp_model* m, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K,
                     int epi = EPI_STORE, const void* R = nullptr) {
   if (m->flop_acc) *m->flop_acc += 2.0 * M * N * K;
   GemmTimer timer(m, 2.0 * M * N * K);
-  const int ranges = m->cfg.dtype == PP_BF16 && !m->force_plain && epi == EPI_STORE ? vocab_ranges(m, M, N, K) : 0;
-  if (ranges) {
-    float* partial = (float*)(m->wsp + m->ws.partial);
-    if (k_gemm_nt_mfma(m->st, A, lda, B, ldb, nullptr, ldc, M, N, K, EPI_STORE, nullptr, 1, ranges, partial) == 0) {
-      k_splitk_reduce_bf16(m->st, partial, C, ldc, M, N, ranges);
-      m->n_mfma++;
-      return;
-    }
-  }
   if (m->cfg.dtype == PP_BF16 && !m->force_plain &&
       k_gemm_nt_mfma(m->st, A, lda, B, ldb, C, ldc, M, N, K, epi, R, 0, 1, nullptr) == 0) { m->n_mfma++; return; }
   m->n_plain++;

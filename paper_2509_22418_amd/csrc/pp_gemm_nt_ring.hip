@@ -358,16 +358,15 @@ static constexpr RingTile kTiles[] = {
 // rounds of 256 units usually wins over the one with the best rate.  Unrolled over the table, so that nothing is divided at run time (this runs for
 // every call; as a loop over the table it took 0.2 of the 4 us that a call takes on the host).
 template <int V = 0>
-static int ring_tile(unsigned M, unsigned N, unsigned steps, int best = 0, long best_cost = 0x7fffffffffffffffl, long* ns = nullptr) {
+static int ring_tile(unsigned M, unsigned N, unsigned steps, int best = 0, long best_cost = 0x7fffffffffffffffl) {
   if constexpr (V < (int)(sizeof(kTiles) / sizeof(kTiles[0]))) {
     constexpr RingTile t = kTiles[V];
     const unsigned tiles = (M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn), per_unit = (tiles + 255) / 256;
     const unsigned full = per_unit / t.per_cu, rest = per_unit % t.per_cu;
     const long step = (long)steps * (tiles >= 256 ? 25600 : 25600 - t.idle * (256 - tiles));          // in 1 / 25600
     const long cost = (long)full * (step * t.step[t.per_cu - 1] / 25600 + t.over_full) + (rest ? step * t.step[rest - 1] / 25600 + t.over : 0);
-    return cost < best_cost ? ring_tile<V + 1>(M, N, steps, V, cost, ns) : ring_tile<V + 1>(M, N, steps, best, best_cost, ns);
+    return cost < best_cost ? ring_tile<V + 1>(M, N, steps, V, cost) : ring_tile<V + 1>(M, N, steps, best, best_cost);
   }
-  if (ns) *ns = best_cost;
   return best;
 }
 
@@ -415,12 +414,6 @@ int k_gemm_swiglu_bwd_ring(hipStream_t st, const void* G, int ldg, const void* W
 int k_gemm_qkv_rope_ring(hipStream_t st, const void* X, int ldx, const void* Wqkv, int ldw, void* qkv, int M, int d, int dh, int K, int S, const float* rope_cos, const float* rope_sin) {
   if (d % 192) return 1;          // a tile is all rotated pairs or none, and no row block is cut
   return launch_fused<EPI_ROPE>(st, X, ldx, Wqkv, ldw, qkv, 3 * d, M, 3 * d, K, nullptr, 3 * d / 192, RingFused{dh / 2, 2 * d, S, nullptr, rope_cos, rope_sin});
-}
-
-long k_gemm_nt_ring_ns(int M, int N, int K) {
-  long ns = 0;
-  ring_tile(M, N, K / 64, 0, 0x7fffffffffffffffl, &ns);
-  return ns;
 }
 
 // bf16 output, epi = EPI_STORE or EPI_ADD_RES (R with leading dimension ldc).  Returns 0 if launched, 1 if the shape is not

@@ -52,7 +52,6 @@ void k_gemm_nt_plain(hipStream_t st, int dtype, const void* A, int lda, const vo
 void k_gemm_nt_plain_splitk(hipStream_t st, int dtype, const void* A, int lda, const void* B, int ldb, float* partial,
                             int M, int N, int K, int splits);
 void k_splitk_reduce(hipStream_t st, const float* partial, float* C, int ldc, int M, int N, int splits);
-void k_splitk_reduce_bf16(hipStream_t st, const float* partial, void* C, int ldc, int M, int N, int splits);          // the same, rounded once
 
 // fp32-multiply MFMA GEMMs, any M, N, K and alignment, fp32 or bf16 storage (pp_gemm_f32.hip; rows of about 8.3 M elements and more go to the
 // vector kernel).  K % splits == 0; splits > 1:
@@ -110,7 +109,6 @@ int k_gemm_nt_ring(hipStream_t st, const void* A, int lda, const void* B, int ld
 int k_gemm_swiglu_fwd_ring(hipStream_t st, const void* X, int ldx, const void* Wgu, int ldw, void* gu, void* a, int M, int F, int K);
 int k_gemm_swiglu_bwd_ring(hipStream_t st, const void* G, int ldg, const void* Wd_rows, int ldw, const void* gu_c0, void* dgu_c0, int ld2f, int half, int M, int N, int K);
 int k_gemm_qkv_rope_ring(hipStream_t st, const void* X, int ldx, const void* Wqkv, int ldw, void* qkv, int M, int d, int dh, int K, int S, const float* rope_cos, const float* rope_sin);
-long k_gemm_nt_ring_ns(int M, int N, int K);          // its time on shapes it takes, estimated
 void gemm_set_small_tiles(int v);      // 1 (default): k_gemm_nt_mfma hands GEMMs with at most 128 tiles of 256 x 256 (half a tile per compute unit) to k_gemm_nt_ring
 void gemm_set_variant(int v);          // 0: register-staged MFMA GEMM, 1: direct-to-LDS MFMA GEMM
 void gemm_set_persistent(int v);       // 1 (default): a workgroup per compute unit walks several tiles when there are more tiles than units

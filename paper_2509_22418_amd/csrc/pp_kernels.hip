@@ -696,8 +696,8 @@ void k_gemm_nt_plain_splitk(hipStream_t st, int dtype, const void* A, int lda, c
 // HBM / Infinity-Cache bound: reads splits * M * N floats once.  Four elements per thread and four partials requested before the first
 // is added (one element and one dependent load at a time: 13.4 us for 16 partials of 512 x 2048, 8 partials of it now 6.9).  The sums run
 // over z in order from +0 either way: same bits.
-template <int VEC, class TO>
-__global__ void splitk_reduce_kernel(const float* __restrict__ partial, TO* __restrict__ C, int ldc, int M, int N, int splits) {
+template <int VEC>
+__global__ void splitk_reduce_kernel(const float* __restrict__ partial, float* __restrict__ C, int ldc, int M, int N, int splits) {
   const size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC;
   const size_t MN = (size_t)M * N;
   if (i >= MN) return;
@@ -725,23 +725,15 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ partial, TO* __re
 #pragma unroll
     for (int e = 0; e < VEC; ++e) s[e] += w[e];
   }
-  TO* o = C + (i / N) * (size_t)ldc + (i % N);          // VEC = 4: N % 4 == 0, so the four stay in one row
-  if constexpr (VEC == 4 && sizeof(TO) == 2) *reinterpret_cast<uint2*>(o) = make_uint2(f32x2_to_bf16x2(s[0], s[1]), f32x2_to_bf16x2(s[2], s[3]));
-  else if constexpr (VEC == 4) *reinterpret_cast<float4*>(o) = make_float4(s[0], s[1], s[2], s[3]);
-  else *o = from_f32<TO>(s[0]);
+  float* o = C + (i / N) * (size_t)ldc + (i % N);          // VEC = 4: N % 4 == 0, so the four stay in one row
+  if constexpr (VEC == 4) *reinterpret_cast<float4*>(o) = make_float4(s[0], s[1], s[2], s[3]);
+  else *o = s[0];
 }
 void k_splitk_reduce(hipStream_t st, const float* partial, float* C, int ldc, int M, int N, int splits) {
   size_t MN = (size_t)M * N;
   if (MN == 0) return;
-  if (N % 4 == 0 && ldc % 4 == 0 && (((uintptr_t)partial | (uintptr_t)C) & 15) == 0) splitk_reduce_kernel<4, float><<<cdiv(MN / 4, 256), 256, 0, st>>>(partial, C, ldc, M, N, splits);
-  else splitk_reduce_kernel<1, float><<<cdiv(MN, 256), 256, 0, st>>>(partial, C, ldc, M, N, splits);
-}
-void k_splitk_reduce_bf16(hipStream_t st, const float* partial, void* C, int ldc, int M, int N, int splits) {
-  const size_t MN = (size_t)M * N;
-  if (MN == 0) return;
-  if (N % 4 == 0 && ldc % 4 == 0 && ((uintptr_t)partial & 15) == 0 && ((uintptr_t)C & 7) == 0)
-    splitk_reduce_kernel<4, bf16_t><<<cdiv(MN / 4, 256), 256, 0, st>>>(partial, (bf16_t*)C, ldc, M, N, splits);
-  else splitk_reduce_kernel<1, bf16_t><<<cdiv(MN, 256), 256, 0, st>>>(partial, (bf16_t*)C, ldc, M, N, splits);
+  if (N % 4 == 0 && ldc % 4 == 0 && (((uintptr_t)partial | (uintptr_t)C) & 15) == 0) splitk_reduce_kernel<4><<<cdiv(MN / 4, 256), 256, 0, st>>>(partial, C, ldc, M, N, splits);
+  else splitk_reduce_kernel<1><<<cdiv(MN, 256), 256, 0, st>>>(partial, C, ldc, M, N, splits);
 }
 
 // ------------------------------------------------------------------------------------------ plain attention
