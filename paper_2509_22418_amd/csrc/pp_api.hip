@@ -578,26 +578,6 @@ static void gemm_dw(pp_model* m, const void* At, const void* Bt, float* G, int M
   k_splitk_reduce(m->st, partial, G, N, M, N, splits);
 }
 
-// K ranges of a token-major bf16 weight gradient of `tiles` 128 x 128 tiles.  As many as one round of the chip takes (512 workgroups, two per unit), in
-// multiples that the kernel can deal to the 8 XCDs by ranges if there is one down to half of that: doubling the ranges until 512 workgroups were reached
-// left most grids a nearly empty second round.  us, doubled / now, without the sum of the ranges, operands out of cache: 768 x 768 over 8192 rows (36 tiles) 25.6 (16 ranges) /
-// 17.9 (12; 13 are 468 workgroups: 23.3), 384 x 768 over 8192 18.9 (32) / 14.6 (16), 768 x 3072 over 3055 33.8 (4) / 23.5 (3), 2304 x 768 over 3055 25.7 (8) / 19.3 (4), 1536 x
-// 2048 over 8192 75.4 (4) / 67.3 (2), 640 x 1280 over 5000 21.6 (16) / 17.1 (8).
-// chain: rows per fp32 sum -- the doubled ranges' length, so that none gets longer than it was with them.
-struct DwRanges { int ranges, kchunk, chain; };
-static DwRanges dw_ranges(long tiles, int K, size_t out_bytes, size_t partial_bytes) {
-  auto chunk = [&](int n) { return ((K + n - 1) / n + 63) / 64 * 64; };
-  auto count = [&](int n) { return (K + chunk(n) - 1) / chunk(n); };
-  int doubled = 1;
-  while (doubled < 32 && tiles * doubled < 512 && (K % (doubled * 2 * 64) == 0 || K % 64) && K / (doubled * 2) >= 256 && out_bytes * (size_t)(doubled * 2) <= partial_bytes) doubled *= 2;
-  int most = (int)std::min({512 / std::max(tiles, 1l), (long)(K / 256), 32l, (long)(partial_bytes / out_bytes)});
-  if (most < 1) most = 1;
-  int n = most;
-  while (n > 1 && 2 * n >= most && tiles * count(n) % 8) --n;
-  if (tiles * count(n) % 8) n = most;
-  return {count(n), chunk(n), chunk(doubled)};
-}
-
 // Weight gradient from token-major operands: G[M x N] (fp32, ld N) = A^T B, A [K x M'] (lda) and B [K x N] (ldb) as the
 // forward / backward passes left them, K = tokens; column m of the product is column (m / m_blk) * a_blk_stride + m % m_blk
 // of A.  The bf16 MFMA kernel gathers its operands with LDS transpose reads, fp32 storage has a token-major kernel too; shapes they do
@@ -611,12 +591,18 @@ static void gemm_dw_tn(pp_model* m, const void* A, int lda, int m_blk, long a_bl
   // over 8192 (4000) 1154 / 1008, 32000 x 768 over 8192 (1500) 441 / 574.  Same bits either way.  A token count that is not a multiple of 64 always
   // comes here: the transposed copies would have rows the NT kernel does not take.
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
+  // The ranges, and with them the order of a gradient's sums, are doubled until the chip has 512 workgroups (two per unit).  Numbers that fill one round better are faster (768 x 768
+  // over 8192 rows, 36 tiles: 26.6 us in 16 ranges, 18.7 in 12; with the sum of the ranges 34.3 / 24.9) but add in another order; the same ranges two to a
+  // workgroup keep the order and gain nothing (25.1, 33.7).
   if (m->cfg.dtype == PP_BF16 && !m->force_plain && m->dw_tn && (tiles <= 256 || K % 64)) {
-    const DwRanges r = dw_ranges(tiles, K, (size_t)M * N * 4, m->ws.partial_bytes);
-    const int kchunk = r.kchunk, ranges = r.ranges;
+    const size_t out_bytes = (size_t)M * N * 4;
+    int splits = 1;
+    while (splits < 32 && tiles * splits < 512 && (K % (splits * 2 * 64) == 0 || K % 64) && K / (splits * 2) >= 256 &&
+           out_bytes * (size_t)(splits * 2) <= m->ws.partial_bytes) splits *= 2;
+    const int kchunk = ((K + splits - 1) / splits + 63) / 64 * 64, ranges = (K + kchunk - 1) / kchunk;
     float* partial = (float*)(m->wsp + m->ws.partial);
     GemmTimer timer(m, 2.0 * M * N * K);
-    if (k_gemm_tn_mfma(m->st, A, lda, m_blk, a_blk_stride, B, ldb, G, N, M, N, K, kchunk, partial, r.chain) == 0) {
+    if (k_gemm_tn_mfma(m->st, A, lda, m_blk, a_blk_stride, B, ldb, G, N, M, N, K, kchunk, partial) == 0) {
       if (ranges > 1) k_splitk_reduce(m->st, partial, G, N, M, N, ranges);
       if (m->flop_acc) *m->flop_acc += 2.0 * M * N * K;
       m->n_mfma++;
