@@ -16,6 +16,8 @@
 #include "pp_kernels.h"
 #include "pp_dev.h"
 
+#include <type_traits>
+
 namespace pp {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -165,9 +167,8 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const T* __restrict__
 
 // ------------------------------------------------------------------------------------------ backward: dQ
 template <int DH, class T>
-__device__ __forceinline__ void attn_bwd_dq_f32(float* ds, const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
+__device__ __forceinline__ void attn_bwd_dq_f32(float* ds, float* Ls, float* Ds, const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
                                                 const T* __restrict__ dO, T* __restrict__ dqkv, int S, int h, int pair, int rank) {
-  float *Ls = ds + 32 * BPITCH, *Ds = Ls + 32;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lh = lane >> 5, l16 = lane & 15, lg = lane >> 4;
   const int qb = (S + 31) / 32 - 1 - rank;
   const int head = pair % h, b = pair / h, q0 = qb * 32, nk = min(S, q0 + 32);
@@ -231,9 +232,8 @@ __device__ __forceinline__ void attn_bwd_dq_f32(float* ds, const T* __restrict__
 
 // ------------------------------------------------------------------------------------------ backward: dK, dV
 template <int DH, class T>
-__device__ __forceinline__ void attn_bwd_dkv_f32(float* Pt, const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
+__device__ __forceinline__ void attn_bwd_dkv_f32(float* Pt, float* DSt, const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
                                                  const T* __restrict__ dO, T* __restrict__ dqkv, int S, int h, int pair, int kb) {
-  float* DSt = Pt + 32 * BPITCH;          // [key][query of the chunk], both
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lh = lane >> 5, l16 = lane & 15, lg = lane >> 4;
   const int head = pair % h, b = pair / h, k0 = kb * 32;
   const int d = h * DH;
@@ -272,10 +272,11 @@ __device__ __forceinline__ void attn_bwd_dkv_f32(float* Pt, const T* __restrict_
       }
     }
     __syncthreads();
-#pragma unroll
-    for (int c = 0; c < NU; ++c) {
+    // as four functions: the loop, inlined into a kernel of this size, is not unrolled in full, and its accumulators are then addressed by index (s_set_gpr_idx)
+    auto unit = [&](auto C) {
+      constexpr int c = decltype(C)::value;
       const int u = wave + 4 * c;
-      if (u * 8 >= DH) continue;
+      if (u * 8 >= DH) return;
       const bool isv = u < DH / 16;
       const int cb = isv ? u : u - DH / 16;
       const T* col = (isv ? dob : base) + cb * 16 + l16;
@@ -283,7 +284,11 @@ __device__ __forceinline__ void attn_bwd_dkv_f32(float* Pt, const T* __restrict_
       // masked: queries before the row's key (first 32 of the first chunk) and the padding of the last piece
       chain(acc[c], isv ? Pt : DSt, BPITCH, n, lane, [&](int i) { return col + (size_t)min(c0 + i, S - 1) * xld; },
             [&](int r, int i) { return c0 + i < k0 + r || c0 + i >= S; }, c0 == k0 || c0 + n > S ? 0 : n, n);
-    }
+    };
+    unit(std::integral_constant<int, 0>{});
+    if constexpr (NU > 1) unit(std::integral_constant<int, 1>{});
+    if constexpr (NU > 2) { unit(std::integral_constant<int, 2>{}); unit(std::integral_constant<int, 3>{}); }
+    static_assert(NU == 1 || NU == 2 || NU == 4, "units per wave");
     __syncthreads();
   }
 #pragma unroll
@@ -304,25 +309,25 @@ __device__ __forceinline__ void attn_bwd_dkv_f32(float* Pt, const T* __restrict_
 
 // ------------------------------------------------------------------------------------------ backward: both in one grid, heaviest blocks first (early keys see the most
 // queries, late queries the most keys).  They share nothing but D, and together they leave fewer units idle behind the longest blocks.  us, two launches / one: 4 x 256, 8 heads of
-// 64 47.5 / 36.9, 1 x 256, 8 heads of 64 46.7 / 27.9, 2 x 1000, 4 heads of 64 140 / 103, 8 x 320, 12 heads of 64 123 / 119, 4 x 128, 16 heads of 32 21 / 15.  At head dim 128 one kernel for both
-// has the registers of the larger: 16 pairs of 600 (304 blocks of 32 rows) 202 / 173, but 16 of 1000 (512) 370 / 404, 128 of 300 (1280) 417 / 437.
+// 64 47.5 / 36.9, 1 x 256, 8 heads of 64 46.7 / 27.9, 2 x 1000, 4 heads of 64 140 / 103, 8 x 320, 12 heads of 64 123 / 119, 4 x 128, 16 heads of 32 21 / 15; fp32, head dim 128: 45 pairs of 378 222 /
+// 208, 25 of 928 0.93 of the two, 120 of 198 (840 blocks of 32 rows) 216 / 218.  Widened bf16 at head dim 128 (tensors on 8-byte boundaries): dQ alone has the registers for two workgroups per
+// unit, which the common kernel has not: 36 pairs of 373 (432 blocks) 133 / 130, 100 of 101 (400) 72.1 / 72.1, 222 of 35 (444) 61.5 / 67.9, 81 of 404 (1053) 306 / 339.
 constexpr unsigned kOneGrid128 = 400;          // blocks of 32 rows
 template <int DH, class T, bool DQ, bool DKV>
-__global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
+__global__ __launch_bounds__(256, DH <= 32 ? 3 : 1) void attn_bwd_f32_kernel(const T* __restrict__ qkv, const float* __restrict__ lse, const float* __restrict__ Dbuf,
                                                            const T* __restrict__ dO, T* __restrict__ dqkv, int S, int h, int n_pairs) {
-  __shared__ float lds[2 * 32 * BPITCH];
-  static_assert(32 * BPITCH >= 64, "room for the statistics of 32 rows");
+  __shared__ float x0[32 * BPITCH], x1[DKV ? 32 * BPITCH : 64];          // dK/dV: P and dS, [key][query of the chunk]; dQ: dS, statistics of 32 rows
   constexpr int KINDS = DQ + DKV;
   const int rank = blockIdx.x / (KINDS * n_pairs), x = blockIdx.x - rank * KINDS * n_pairs;
-  if (DKV && x < n_pairs) attn_bwd_dkv_f32<DH>(lds, qkv, lse, Dbuf, dO, dqkv, S, h, x, rank);
-  else if (DQ) attn_bwd_dq_f32<DH>(lds, qkv, lse, Dbuf, dO, dqkv, S, h, DKV ? x - n_pairs : x, rank);
+  if (DKV && x < n_pairs) attn_bwd_dkv_f32<DH>(x0, x1, qkv, lse, Dbuf, dO, dqkv, S, h, x, rank);
+  else if (DQ) attn_bwd_dq_f32<DH>(x0, x1, x1 + 32, qkv, lse, Dbuf, dO, dqkv, S, h, DKV ? x - n_pairs : x, rank);
 }
 template <int DH, class T>
 static void bwd_f32(hipStream_t st, const void* qkv, const float* lse, const float* Dbuf, const void* dO, void* dqkv, int B, int S, int h) {
   const unsigned blocks = (unsigned)B * h * ((S + 31) / 32);
-  if (DH < 128 || blocks <= kOneGrid128) {
+  if (DH < 128 || sizeof(T) == 4 || blocks <= kOneGrid128) {
     attn_bwd_f32_kernel<DH, T, true, true><<<2 * blocks, 256, 0, st>>>((const T*)qkv, lse, Dbuf, (const T*)dO, (T*)dqkv, S, h, B * h);
-  } else if constexpr (DH == 128) {
+  } else if constexpr (DH == 128 && sizeof(T) == 2) {
     attn_bwd_f32_kernel<DH, T, true, false><<<blocks, 256, 0, st>>>((const T*)qkv, lse, Dbuf, (const T*)dO, (T*)dqkv, S, h, B * h);
     attn_bwd_f32_kernel<DH, T, false, true><<<blocks, 256, 0, st>>>((const T*)qkv, lse, Dbuf, (const T*)dO, (T*)dqkv, S, h, B * h);
   }
