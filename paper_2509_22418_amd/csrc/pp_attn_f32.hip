@@ -356,13 +356,27 @@ static int fwd_f32(hipStream_t st, const void* qkv, void* o, float* lse, int B, 
            else if (dh == 64) { constexpr int DH = 64; CALL; } else { constexpr int DH = 128; CALL; } }                                     \
   } while (0)
 
-// Few rows, short rows: the vector kernels run a workgroup per row, all at once up to about 3000 of them, and then last as long as one row;
-// here a workgroup of 32 rows is a chain of three dependent phases.  For the forward the number of rows is what counts, for the backward, whose vector chain is
-// longer, pairs x S^2 (pairs = B h).  The lines below are where both took the same time (pairs 1 .. 96, S 33 .. 256; fp32, us, vector / these):
-//   forward   dh 16: 64 x 64 8.2 / 8.9, 96 x 64 11.0 / 9.0      dh 64: 16 x 160 16.1 / 17.9, 16 x 256 32 / 21      dh 128: 4 x 256 23.6 / 30.3, 64 x 48 13.4 / 14.8, 64 x 64 22 / 16
-//   backward  dh 16: 4 x 48 7.9 / 8.2, 16 x 33 8.2 / 8.0     dh 32: 16 x 48 9.2 / 10.5, 4 x 160 19.1 / 15.4     dh 64: 16 x 64 14.6 / 16.1, 4 x 160 25.3 / 24.3     dh 128: 4 x 160 38.6 / 46.8, 64 x 48 43.4 / 28.8
-static bool fwd_pays(long pairs, int S, int dh) { return pairs * S >= (dh == 16 ? 4608 : 3444); }
-static bool bwd_pays(long pairs, int S, int dh) { return pairs * S * S >= (dh == 16 ? 10000 : dh == 32 ? 46000 : dh == 64 ? 78000 : 110000); }
+// Few rows, short rows: the vector kernels run a workgroup per row, all at once up to about 3000 of them; then they last as long as one row, and beyond that their time grows with rows x
+// length.  Here a workgroup of 32 rows is a chain of dependent phases over the keys, 128 at a time, whatever the number of rows (pairs = B h).  So the lines are pairs x S x (S + b) >= c x (S rounded up to
+// 128 + d), where both took the same time; for the backward of head dims 16 and 32, whose vector chain is short, pairs x (S + b)^3.  Rows of fewer than 8 to 18 positions stay with the vector kernels
+// whatever their number: most of a block of 32 would be padding.  From 820 shapes per head dim (pairs 1 .. 32768, S 1 .. 1184, fp32 and bf16), 98 % of which run on the faster kernel or within 3 % of it; the
+// nearest and the far ends (fp32, us, vector / these):
+//   forward   dh 16: 64 x 64 8.8 / 9.5, 3 x 850 31 / 38, 16 x 256 19.7 / 16.3, 4 x 1150 67 / 48      dh 32: 48 x 80 9.9 / 10.9, 12 x 256 22 / 18, 4 x 850 51 / 41      dh 64: 16 x 160 16.6 / 18.5, 2 x 850
+//             46 / 49, 32768 x 4 191 / 381, 16 x 200 23 / 19, 12 x 256 34 / 21, 4 x 850 80 / 50      dh 128: 16 x 160 26.7 / 27.2, 1 x 1150 77 / 98, 16 x 200 37 / 28, 12 x 256 63 / 31, 2 x 1150 128 / 99
+//   backward  dh 16: 20 x 34 7.9 / 8.9, 1 x 128 11.0 / 9.1      dh 32: 18 x 53 10.4 / 11.0, 3 x 160 17.0 / 15.8      dh 64: 2 x 200 22.5 / 27.4, 1 x 420 38 / 43, 32 x 48 15.2 / 16.6      dh 128: 8 x 100
+//             28.7 / 29.9, 2 x 256 42 / 47, 1 x 420 53 / 73, 128 x 24 33 / 23
+static bool fwd_pays(long pairs, int S, int dh) {
+  const int b = dh == 16 ? 256 : dh == 32 ? 96 : 64, d = dh == 16 ? 256 : 128, c = dh == 16 ? 3500 : dh == 32 ? 2500 : dh == 64 ? 1560 : 1275;
+  return S >= 8 && pairs * S * (S + b) >= (long)c * ((S + 127) / 128 * 128 + d);
+}
+static bool bwd_pays(long pairs, int S, int dh) {
+  if (dh <= 32) {
+    const double l = S + dh, line = dh == 16 ? 144 : 224;
+    return S >= 8 && (double)pairs * l * l * l >= line * line * line;
+  }
+  const int d = dh == 64 ? 256 : 128, c = dh == 64 ? 269 : 388;
+  return S >= (dh == 64 ? 12 : 18) && pairs * S * (S + 32) >= (long)c * ((S + 127l) / 128 * 128 + d);
+}
 // The scores of 32 queries against the whole sequence sit in LDS: sequences of more than MAX_S positions return 1.
 int k_attn_fwd_f32(hipStream_t st, int dtype, const void* qkv, void* o, float* lse, int B, int S, int h, int dh) {
   if (S > MAX_S || !shapes_ok(dtype, qkv, o, S, h, dh) || !fwd_pays((long)B * h, S, dh)) return 1;

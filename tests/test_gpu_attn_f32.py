@@ -4,13 +4,14 @@ import pytest
 import torch
 
 import paper_2509_22418_amd as pp
+from test_gpu_attn_f32_lines import runs_on_mfma
 
 pytestmark = pytest.mark.gpu
 
-# (B, S, h, dh), enough rows each that both directions take these kernels: single positions, one short of / past a block, past a chunk, and
-# around the last length whose scores fit LDS (1184; the forward of 1185 is the plain kernel's)
-CASES = [(131072, 1, 1, 16), (12, 31, 12, 32), (1, 33, 64, 64), (2, 128, 2, 128), (1, 161, 12, 16), (1, 257, 2, 128), (1, 1152, 1, 32), (1, 1153, 1, 64), (1, 1184, 1, 128), (1, 1184, 1, 16),
-         (1, 1185, 1, 32)]
+# (B, S, h, dh), enough rows each that both directions take these kernels (asserted): the shortest rows taken, one short of / past a block, past a chunk, and
+# around the last length whose scores fit LDS (1184; the forward of 1185 is the plain kernel's); single positions, which stay with the plain kernels in any number
+CASES = [(4096, 8, 1, 16), (24, 31, 12, 32), (2, 33, 64, 64), (8, 128, 2, 128), (3, 161, 12, 16), (5, 257, 2, 128), (3, 1152, 1, 32), (2, 1153, 1, 64), (2, 1184, 1, 128), (4, 1184, 1, 16),
+         (1, 1185, 1, 32), (131072, 1, 1, 16)]
 
 
 def run(qkv, dO, B, S, h, dh, dt, path):
@@ -32,6 +33,7 @@ def test_same_bits_as_the_plain_kernels(B, S, h, dh, dtype):
     g = torch.Generator(device="cuda").manual_seed(3)
     off = 4 if dtype == "bf16" and dh >= 64 else 0          # 8 bytes off a 16-byte boundary: not taken by the bf16 kernels
     qkv, dO = (torch.randn(n + off, device="cuda", generator=g).to(td)[off:] for n in (B * S * 3 * h * dh, B * S * h * dh))
+    assert runs_on_mfma(dt, qkv, dO, B, S, h, dh) == (int(1 < S <= 1184), int(S > 1))
     for a, b in zip(run(qkv, dO, B, S, h, dh, dt, 0), run(qkv, dO, B, S, h, dh, dt, 1)):
         assert torch.equal(a, b)
 
@@ -40,12 +42,13 @@ def test_same_bits_as_the_plain_kernels(B, S, h, dh, dtype):
 def test_values_that_are_not_finite_stay_behind_the_mask(value):
     """One position whose q, k, v and dO are not finite: earlier queries do not see it, later keys are not reached by it, and every
     output equals the plain kernels' (NaN where they have NaN)."""
-    B, S, h, dh, at = 1, 150, 8, 32, 70
+    B, S, h, dh, at = 1, 150, 32, 32, 70
     g = torch.Generator(device="cuda").manual_seed(4)
     qkv = torch.randn((S, 3 * h * dh), device="cuda", generator=g)
     dO = torch.randn((S, h * dh), device="cuda", generator=g)
     qkv[at, 5::7] = value
     dO[at, 3] = value
+    assert runs_on_mfma(pp.PP_F32, qkv, dO, B, S, h, dh) == (1, 1)
     got, ref = run(qkv, dO, B, S, h, dh, pp.PP_F32, 0), run(qkv, dO, B, S, h, dh, pp.PP_F32, 1)
     assert bool(torch.isfinite(ref[0][:at]).all()) and not bool(torch.isfinite(ref[0][at:]).all())
     for a, b in zip(got, ref):
