@@ -642,26 +642,32 @@ static int launch_dl(hipStream_t st, const void* A, int lda, const void* B, int 
   return 0;
 }
 
-// Whether a fused GEMM is faster on the ring's 128 x 192 tiles (two workgroups per unit) than on 256 x 256 ones: both estimated in ns from the times of 16 shapes
-// (M = 40 .. 16384, K = 256 .. 2048, weights out of cache), and taken if it is below pct % of the big tiles'.  A round of big tiles costs b0 + K (b1 + b2 * its
-// fill), of small ones s2 = two per unit or s1 = one, a partly filled second place in between.  us, big / small: SwiGLU forward 3055 x 3072, K = 768 (288 big tiles) 43.9 / 36.4,
-// 200 x 3072 19.4 / 13.7, against 8192 x 3072 (768, three full rounds) 82.9 / 115; backward 8192 x 3072, K = 768 (384) 69.4 / 65.3, 3055 x 3072 31.9 / 27.1, 2000 x 2048, K = 512
-// 23.8 / 14.6, against 8192 x 2048 (256) 38.0 / 41.3; q|k|v with rotation 8192 x 768 (288) 50.4 / 36.1, 3055 x 768 26.4 / 22.6, 16384 x 768 74.3 / 68.2.
-struct FusedCost { long b0, b1, b2, bf, s2, s2k, s1, s1k, s1f; };          // ns, ns per K element; bf: part of the fill's cost that does not grow with K
-static constexpr FusedCost kFusedFwd{8000, 14500, 10500, 0, 5000, 29000, 4000, 12500, 6000}, kFusedBwd{14000, 13500, 10500, 10000, 8000, 33000, 5000, 12500, 7500};          // per K: 1 / 1000 ns
-static bool fused_on_ring(const FusedCost& c, long big, long small, long K, long pct) {
+// Whether a fused GEMM is faster on the ring's 128 x 192 tiles (two workgroups per unit) than on 256 x 256 ones: both estimated in ns, and the smaller taken.  A round of big tiles
+// costs b0 + K (b1 + b2 * its fill) and a part bf of the fill that does not grow with K, of small ones s2 = two per unit or s1 = one, a partly filled second place in between.  Fitted to
+// 2900 shapes timed on both kernels (M = 24 .. 16384, K = 64 .. 3072, weights out of cache; the rotary one at d = 768 .. 3840): where the small tiles are taken they are the faster ones or
+// within 3 % (rotary 5 %), where the big ones are, within 6 % (SwiGLU forward 15 %).  us, big / small: SwiGLU forward 3055 x 3072, K = 768 (288 big tiles) 43.9 / 36.4, 200 x 3072 19.4 / 13.7, 1625 x 4936,
+// K = 1088 69 / 55, against 8192 x 3072 (768, three full rounds) 82.9 / 115, 3470 x 6128, K = 2368 196 / 207; backward 8192 x 3072, K = 768 (384) 69.4 / 65.3, 3055 x 3072 31.9 / 27.1, 2000 x 2048,
+// K = 512 23.8 / 14.6, against 8192 x 2048 (256) 38.0 / 41.3, 4894 x 2800, K = 320 28.9 / 31.8, 3847 x 8096, K = 448 68 / 76; q|k|v with rotation 8192 x 768 (288) 50.4 / 36.1, 3055 x 768 26.4 / 22.6,
+// 16384 x 768 74.3 / 68.2, against 1000 x 3072 (144) 70 / 76, 2967 x 1536 (216) 44 / 62, 753 x 3840 87 / 93.
+struct FusedCost { long b0, b1, b2, bf, s2, s2k, s1, s1k, s1f; };          // ns, ns per 1000 K elements
+static constexpr FusedCost kFusedFwd{7100, 14500, 12200, 3600, 9100, 21700, 5100, 10000, 8400}, kFusedBwd{11100, 16800, 6700, 12500, 16600, 19300, 5800, 10000, 12400},
+    kFusedRope{10800, 19600, 1500, 0, 0, 25700, 6400, 8800, 12200};
+// n: hidden units (EPI_SWIGLU), columns (EPI_SWIGLU_BWD), d (EPI_ROPE)
+bool gemm_fused_on_ring(int epi, int M, int n, int K) {
   if (g_gemm_small_tiles.load(std::memory_order_relaxed) == 0) return false;
+  const FusedCost& c = epi == EPI_SWIGLU ? kFusedFwd : epi == EPI_SWIGLU_BWD ? kFusedBwd : kFusedRope;
+  const long big = (M + 255l) / 256 * (epi == EPI_SWIGLU ? (n + 127l) / 128 : epi == EPI_SWIGLU_BWD ? (n + 255l) / 256 : 3l * n / 256);
+  const long small = (M + 127l) / 128 * (epi == EPI_SWIGLU ? (n + 95l) / 96 : epi == EPI_SWIGLU_BWD ? (n + 191l) / 192 : 3l * n / 192);
   const long rounds = (big + 255) / 256, t_big = rounds * (c.b0 + c.b1 * K / 1000) + big * (c.bf + c.b2 * K / 1000) / 256;
   const long full = small / 512, rest = small % 512, t2 = c.s2 + c.s2k * K / 1000, t1 = c.s1 + (c.s1k + c.s1f * std::min(rest, 256l) / 256) * K / 1000;
-  const long t_small = full * t2 + (rest ? t1 + std::max(t2 - t1, 0l) * std::max(rest - 256, 0l) / 256 : 0);
-  return 100 * t_small < pct * t_big;
+  return full * t2 + (rest ? t1 + std::max(t2 - t1, 0l) * std::max(rest - 256, 0l) / 256 : 0) < t_big;
 }
 
 // gu[M x 2F] (ld 2F) = X[M x K] [Wg; Wu]^T and a[M x F] = silu(gate) * up in one launch; Wgu = the 2F x K stack
 int k_gemm_swiglu_fwd_mfma(hipStream_t st, const void* X, int ldx, const void* Wgu, int ldw, void* gu, void* a, int M, int F, int K) {
   if (g_gemm_variant.load(std::memory_order_relaxed) != 1 || M < 1 || F < 8 || (F & 7) || K < DL_BK || K % DL_BK || (ldx & 7) || (ldw & 7)) return 1;
   if (((uintptr_t)X | (uintptr_t)Wgu | (uintptr_t)gu | (uintptr_t)a) & 15) return 1;
-  if (fused_on_ring(kFusedFwd, ((M + 255l) / 256) * ((F + 127l) / 128), ((M + 127l) / 128) * ((F + 95l) / 96), K, 97) && k_gemm_swiglu_fwd_ring(st, X, ldx, Wgu, ldw, gu, a, M, F, K) == 0) return 0;
+  if (gemm_fused_on_ring(EPI_SWIGLU, M, F, K) && k_gemm_swiglu_fwd_ring(st, X, ldx, Wgu, ldw, gu, a, M, F, K) == 0) return 0;
   static LdsOptIn opt_in;
   auto kern = gemm_nt_mfma_dl_kernel<EPI_SWIGLU, false>;
   if (!opt_in(reinterpret_cast<const void*>(kern), DL_LDS_BYTES)) return 1;
@@ -676,7 +682,7 @@ int k_gemm_swiglu_bwd_mfma(hipStream_t st, const void* G, int ldg, const void* W
                            int M, int N, int K) {
   if (g_gemm_variant.load(std::memory_order_relaxed) != 1 || M < 1 || N < 8 || (N & 7) || (ld2f & 7) || (half & 7) || K < DL_BK || K % DL_BK || (ldg & 7) || (ldw & 7)) return 1;
   if (((uintptr_t)G | (uintptr_t)Wd_rows | (uintptr_t)gu_c0 | (uintptr_t)dgu_c0) & 15) return 1;
-  if (fused_on_ring(kFusedBwd, ((M + 255l) / 256) * ((N + 255l) / 256), ((M + 127l) / 128) * ((N + 191l) / 192), K, 95) && k_gemm_swiglu_bwd_ring(st, G, ldg, Wd_rows, ldw, gu_c0, dgu_c0, ld2f, half, M, N, K) == 0) return 0;
+  if (gemm_fused_on_ring(EPI_SWIGLU_BWD, M, N, K) && k_gemm_swiglu_bwd_ring(st, G, ldg, Wd_rows, ldw, gu_c0, dgu_c0, ld2f, half, M, N, K) == 0) return 0;
   static LdsOptIn opt_in;
   auto kern = gemm_nt_mfma_dl_kernel<EPI_SWIGLU_BWD, false>;
   if (!opt_in(reinterpret_cast<const void*>(kern), DL_LDS_BYTES)) return 1;
@@ -690,7 +696,7 @@ int k_gemm_qkv_rope_mfma(hipStream_t st, const void* X, int ldx, const void* Wqk
   if (g_gemm_variant.load(std::memory_order_relaxed) != 1 || M < 1 || S < 1 || d < BN || d % BN || (dh != 64 && dh != 128 && dh != 256) || d % dh) return 1;
   if (K < DL_BK || K % DL_BK || (ldx & 7) || (ldw & 7) || !rope_cos || !rope_sin) return 1;
   if (((uintptr_t)X | (uintptr_t)Wqkv | (uintptr_t)qkv | (uintptr_t)rope_cos | (uintptr_t)rope_sin) & 15) return 1;
-  if (fused_on_ring(kFusedFwd, ((M + 255l) / 256) * (3l * d / 256), ((M + 127l) / 128) * (3l * d / 192), K, 110) && k_gemm_qkv_rope_ring(st, X, ldx, Wqkv, ldw, qkv, M, d, dh, K, S, rope_cos, rope_sin) == 0) return 0;
+  if (gemm_fused_on_ring(EPI_ROPE, M, d, K) && k_gemm_qkv_rope_ring(st, X, ldx, Wqkv, ldw, qkv, M, d, dh, K, S, rope_cos, rope_sin) == 0) return 0;
   static LdsOptIn opt_in;
   auto kern = gemm_nt_mfma_dl_kernel<EPI_ROPE, false>;
   if (!opt_in(reinterpret_cast<const void*>(kern), DL_LDS_BYTES)) return 1;

@@ -105,7 +105,8 @@ int k_gemm_tn_mfma(hipStream_t st, const void* A, int lda, int m_blk, long a_blk
                    int M, int N, int K, int kchunk, float* partial, int sub = 0x40000000);          // sub: rows per running fp32 sum (a multiple of 64)
 // smaller tiles (32 x 64 to 128 x 256, chosen by shape) for shapes with too few 256 x 256 tiles to fill the chip (bf16 out, EPI_STORE / EPI_ADD_RES)
 int k_gemm_nt_ring(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, int epi, const void* R);
-// the fused GEMMs on the same tiles; arguments as, and checked by, k_gemm_swiglu_fwd_mfma, k_gemm_swiglu_bwd_mfma and k_gemm_qkv_rope_mfma
+// the fused GEMMs on the same tiles where gemm_fused_on_ring says so; arguments as, and checked by, k_gemm_swiglu_fwd_mfma, k_gemm_swiglu_bwd_mfma and k_gemm_qkv_rope_mfma
+bool gemm_fused_on_ring(int epi, int M, int n, int K);
 int k_gemm_swiglu_fwd_ring(hipStream_t st, const void* X, int ldx, const void* Wgu, int ldw, void* gu, void* a, int M, int F, int K);
 int k_gemm_swiglu_bwd_ring(hipStream_t st, const void* G, int ldg, const void* Wd_rows, int ldw, const void* gu_c0, void* dgu_c0, int ld2f, int half, int M, int N, int K);
 int k_gemm_qkv_rope_ring(hipStream_t st, const void* X, int ldx, const void* Wqkv, int ldw, void* qkv, int M, int d, int dh, int K, int S, const float* rope_cos, const float* rope_sin);

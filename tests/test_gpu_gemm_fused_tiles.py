@@ -1,5 +1,7 @@
 """The SwiGLU and rotary GEMMs on small tiles give the bits of the big-tile kernels: whole steps of models whose token counts, widths and hidden units end in the
 middle of a tile, with the smaller-tile kernels on and off."""
+import ctypes
+
 import pytest
 import torch
 
@@ -23,6 +25,11 @@ def test_same_bits_as_big_tiles(d, h, ff, B, S, mname):
     if S == 1:
         tgt[:] = 7
     weights, out = gen.make_weights(cfg, seed=5), []
+    on_small = ctypes.CDLL(pp.lib_path())["_ZN2pp18gemm_fused_on_ringEiiii"]
+    on_small.restype = ctypes.c_bool
+    pp.pp_set_option(None, "gemm_small_tiles", 1)
+    n = ff if mname == "all" else mask["ffn_hi"] - mask["ffn_lo"]
+    assert on_small(2, B * S, ff, d) and on_small(3, B * S, n, d) and on_small(4, B * S, d, d)          # SwiGLU, its backward, rotary: the second pass is on small tiles
     for small in (0, 1):
         pp.pp_set_option(None, "gemm_variant", 1)
         pp.pp_set_option(None, "gemm_small_tiles", small)
