@@ -282,10 +282,12 @@ constexpr long kLargeTiles = 512;
 // Up to kDeepTiles 32 x 32 tiles of fp32 K-contiguous operands the fragments are read a step ahead (DEEP, 132 registers a wave): with one or two workgroups per
 // unit nothing else covers the reads and stores of a step.  us without / with: 1024 x 512 (512 tiles), K = 2048 32.1 / 26.3, K = 8000 101 / 80.5; 1024 x 1536 (1536), K = 512
 // 19.7 / 18.7; from there on the workgroups that the registers cost are worth more: 1024 x 2048 (2048) 23.2 / 24.2, and so they are with 64 x 64 tiles
-// (1024 x 4096, K = 512 39.7 / 49.1, 168 registers).  Short ranges lose to the longer code (128 x 64, K = 64 3.8 / 4.2; K = 256 4.3 / 4.0), token-major panels, read four bytes at a
-// time, gain nothing (512 x 512 over 1024 in ranges of 256: 9.9 / 10.6), and widened bf16 operands would be waited for right behind their requests (1000 x 520, K = 1000 21.7 / 23.2).
+// (1024 x 4096, K = 512 39.7 / 49.1, 168 registers).  Short ranges lose to the longer code (128 x 64, K = 64 3.8 / 4.2; K = 256 4.3 / 4.0): 448 it takes on more than 600 tiles (1170 x 1000,
+// K = 320 14.6 / 15.1, while 1024 x 1536, K = 512 gains) and where rows are loaded element by element (VEC = false: 49 x 254, K = 263 7.5 / 8.1, 1748 x 146, K = 285 12.0 / 12.7, 176 x 152, K = 429
+// 9.3 / 9.6, from 448 on 0.92 to 0.95 of the plain loop's time), else 256.  Token-major panels, read four bytes at a time, gain nothing (512 x 512 over 1024 in ranges of 256: 9.9 / 10.6), and
+// widened bf16 operands would be waited for right behind their requests (1000 x 520, K = 1000 21.7 / 23.2).
 constexpr long kDeepTiles = 1536;
-constexpr int kDeepRange = 256;
+bool gemm_f32_reads_ahead(long tiles, int range, bool vec) { return tiles <= kDeepTiles && range >= (vec && tiles <= 600 ? 256 : 448); }
 
 template <class T, class TO, bool TN, bool VEC>
 static void launch_f32(hipStream_t st, const void* A, const void* B, void* C, const void* R, const F32GemmArgs& g, int splits) {
@@ -294,7 +296,7 @@ static void launch_f32(hipStream_t st, const void* A, const void* B, void* C, co
   const dim3 grid32((g.N + 31) / 32, (g.M + 31) / 32, splits);
   if (t64 >= kLargeTiles)
     gemm_f32_mfma_kernel<T, TO, TN, false, VEC, false><<<dim3((g.N + 63) / 64, (g.M + 63) / 64, splits), 256, 0, st>>>((const T*)A, (const T*)B, (TO*)C, (const T*)R, g);
-  else if (kDeep && (long)grid32.x * grid32.y * grid32.z <= kDeepTiles && g.kchunk >= kDeepRange)
+  else if (kDeep && gemm_f32_reads_ahead((long)grid32.x * grid32.y * grid32.z, g.kchunk, VEC))
     gemm_f32_mfma_kernel<T, TO, TN, true, VEC, kDeep><<<grid32, 256, 0, st>>>((const T*)A, (const T*)B, (TO*)C, (const T*)R, g);
   else
     gemm_f32_mfma_kernel<T, TO, TN, true, VEC, false><<<grid32, 256, 0, st>>>((const T*)A, (const T*)B, (TO*)C, (const T*)R, g);

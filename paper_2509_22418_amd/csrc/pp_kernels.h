@@ -58,6 +58,7 @@ void k_splitk_reduce(hipStream_t st, const float* partial, float* C, int ldc, in
 // `partial` receives [splits][M][N] floats and C is not written (k_splitk_reduce sums them).
 void k_gemm_nt_f32(hipStream_t st, int dtype, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, int epi, const void* R,
                    int out_f32, int splits, float* partial);
+bool gemm_f32_reads_ahead(long tiles, int range, bool vec);          // which of its loops runs on `tiles` of 32 x 32; vec: rows are whole aligned groups of four
 // C[M x N] fp32 = A^T B, A's columns in blocks as in k_gemm_tn_mfma; returns 1 (nothing launched) if M > m_blk and a group of four
 // columns could straddle two blocks, or if rows are too long
 int k_gemm_tn_f32(hipStream_t st, const float* A, int lda, int m_blk, long a_blk_stride, const float* B, int ldb, float* C, int ldc, int M, int N, int K,

@@ -14,7 +14,7 @@ def test_same_bits_as_the_plain_kernel(M, N, K):
     check(M, N, K, (K + 3) // 4 * 4, 1)
 
 
-@pytest.mark.parametrize("M,N,K,ld,splits", [(65, 130, 512, 513, 1), (65, 130, 1024, 1024, 2), (200, 72, 1280, 1281, 4), (31, 33, 260, 262, 1)])
+@pytest.mark.parametrize("M,N,K,ld,splits", [(65, 130, 512, 513, 1), (65, 130, 1024, 1024, 2), (200, 72, 1280, 1281, 4), (200, 72, 2048, 2049, 4), (31, 33, 260, 262, 1), (31, 33, 511, 514, 1)])
 def test_unaligned_rows_and_split_ranges(M, N, K, ld, splits):
     check(M, N, K, ld, splits)
 

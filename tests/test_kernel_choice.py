@@ -37,3 +37,22 @@ def test_fused_gemms_run_on_the_faster_tiles(epi, M, n, K, small):
     off = f(epi, M, n, K)
     pp.pp_set_option(None, "gemm_small_tiles", 1)
     assert not off
+
+
+# (M, N, K, rows in whole groups of four, fragments a step ahead): us, plain loop / a step ahead
+F32 = [(1024, 512, 2048, True, True),           # 32.1 / 26.3
+       (1024, 1536, 512, True, True),           # 19.7 / 18.7
+       (128, 64, 256, True, True),              # 4.3 / 4.0
+       (128, 64, 64, True, False),              # 3.8 / 4.2
+       (1024, 2048, 512, True, False),          # 23.2 / 24.2
+       (1170, 1000, 320, True, False),          # 14.6 / 15.1
+       (49, 254, 263, False, False),            # 7.5 / 8.1
+       (1748, 146, 285, False, False),          # 12.0 / 12.7
+       (308, 30, 271, False, False)]            # 7.1 / 7.6
+
+
+@pytest.mark.parametrize("M,N,K,vec,ahead", F32)
+def test_fp32_gemm_runs_the_faster_loop(M, N, K, vec, ahead):
+    f = ctypes.CDLL(pp.lib_path())["_ZN2pp20gemm_f32_reads_aheadElib"]
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_long, ctypes.c_int, ctypes.c_bool]
+    assert f(-(-M // 32) * -(-N // 32), K, vec) == ahead
