@@ -370,6 +370,8 @@ static int ring_tile(unsigned M, unsigned N, unsigned steps, int best = 0, long 
   return best;
 }
 
+int gemm_ring_tile(int M, int N, int K) { return ring_tile(M, N, K / 64); }
+
 // B is touched ahead from K = 2048 on, by the tiles of one workgroup per unit: below that it costs what it saves (3055 x 768, K = 768: 8.3 us without, 8.5 with; its
 // code alone 0.5 of the 4.3 us of a K of 64), and the tiles of several workgroups per unit, which are at different K already, lose as often as they gain (3055 x 768 in
 // 64 x 96 tiles, K = 3072: 24.7 / 27.8).

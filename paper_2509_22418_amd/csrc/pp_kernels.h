@@ -105,6 +105,7 @@ int k_gemm_nt_mfma(hipStream_t st, const void* A, int lda, const void* B, int ld
 int k_gemm_tn_mfma(hipStream_t st, const void* A, int lda, int m_blk, long a_blk_stride, const void* B, int ldb, float* C, int ldc,
                    int M, int N, int K, int kchunk, float* partial, int sub = 0x40000000);          // sub: rows per running fp32 sum (a multiple of 64)
 // smaller tiles (32 x 64 to 128 x 256, chosen by shape) for shapes with too few 256 x 256 tiles to fill the chip (bf16 out, EPI_STORE / EPI_ADD_RES)
+int gemm_ring_tile(int M, int N, int K);          // which of its eight tiles, 0 = 32 x 64 .. 7 = 128 x 256
 int k_gemm_nt_ring(hipStream_t st, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, int epi, const void* R);
 // the fused GEMMs on the same tiles where gemm_fused_on_ring says so; arguments as, and checked by, k_gemm_swiglu_fwd_mfma, k_gemm_swiglu_bwd_mfma and k_gemm_qkv_rope_mfma
 bool gemm_fused_on_ring(int epi, int M, int n, int K);

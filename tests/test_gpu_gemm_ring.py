@@ -1,4 +1,4 @@
-"""The smaller-tile NT GEMM at the edges of its five tiles: one row or column past a tile, one K step and fewer steps than the ring has
+"""The smaller-tile NT GEMM at the edges of its tiles: one row or column past a tile, one K step and fewer steps than the ring has
 stages, column counts that 16-byte stores do not take, residual; against fp64 on the same bf16 inputs."""
 import pytest
 import torch
@@ -9,11 +9,12 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # M, N, K, residual (tile that the dispatch picks)
-    (1, 8, 64, False), (65, 63, 128, True), (1003, 768, 192, False),        # 64 x 64
-    (3055, 772, 256, True), (3054, 761, 320, False),                         # 64 x 96
+    (1, 8, 64, False), (65, 63, 128, True),                                  # 32 x 64
+    (1003, 768, 192, False),                                                 # 64 x 64
+    (3055, 772, 256, True), (3054, 761, 320, False),                         # 64 x 192
     (2048, 2040, 64, True), (2047, 1921, 320, False),                        # 128 x 128
     (8192, 768, 64, True), (8191, 761, 448, False),                          # 128 x 192
-    (4096, 2048, 128, False), (4095, 2047, 256, True),                       # 256 x 128
+    (4096, 2048, 128, False), (4095, 2047, 256, True),                       # 128 x 256
 ]
 
 
