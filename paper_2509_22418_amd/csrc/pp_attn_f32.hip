@@ -11,7 +11,7 @@
 // Work split: one workgroup per 32 queries (forward, dQ) or 32 keys (dK, dV) of a head.  Its four waves share the score tiles
 // (32 x 32 each, operands straight from global memory: 32 MFMAs of 64 cycles at head dim 64 against 16 loads), leave them in LDS, and then
 // own 16 columns of the output each (16x16x4 MFMAs: 8 cycles per chain step, two row blocks in flight).  Bound by the
-// chain of dependent phases and keys of one block (matrix pipe busy 0.12 to 0.24, waves waiting 0.52 to 0.56 in the call below: profiles/op_kernels_pmc.txt).
+// chain of dependent phases and keys of one block (matrix pipe busy 0.12 to 0.25, waves waiting 0.50 to 0.56 in the call below: profiles/op_kernels_pmc.txt).
 // 4 x 256 tokens, 8 heads of 64, fp32 (us, vector kernels / these): forward 246 / 20.9, dQ 561 / 21.6, dK and dV 577 / 25.5.
 #include "pp_kernels.h"
 #include "pp_dev.h"

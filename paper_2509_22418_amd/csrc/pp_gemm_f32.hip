@@ -20,7 +20,7 @@
 // Not taken: rows so long that a tile's offsets pass 31 bits (offsets_fit: about 8.3 M elements), and TN column blocks that are not
 // multiples of 4.  An NT panel row is cut into groups of 8 (16) k; the 16-byte chunk i of a group holds the k
 // that lane group i needs (k = i mod 2, resp. mod 4), so one 16-byte read feeds four MFMAs.  Chunks are permuted by row so that 16
-// rows of one chunk lie on different banks; all the same a third of the kernel's LDS-active cycles are counted as conflicts (LDS active 0.31 to 0.49, matrix pipe
+// rows of one chunk lie on different banks; all the same a third of the kernel's LDS-active cycles are counted as conflicts (LDS active 0.31 to 0.50, matrix pipe
 // busy 0.53 with 32 x 32 tiles without DEEP and 0.64 with it, 0.81 with 64 x 64: profiles/op_kernels_pmc.txt).  TN panels are stored [k][m] as they lie
 // in memory, with bit 5 (bit 4) of m flipped for every second k (pair of k), and are read 4 bytes per lane.
 #include "pp_kernels.h"

@@ -732,7 +732,9 @@ int k_gemm_nt_mfma(hipStream_t st, const void* A, int lda, const void* B, int ld
   if (out_f32) return epi == EPI_STORE ? launch<EPI_STORE, true>(st, A, lda, B, ldb, C, ldc, M, N, Ksplit, nullptr, 1) : 1;
   // At most half a tile of 256 x 256 per compute unit (d_model 768: 96 tiles for 256 units): smaller tiles fill the chip
   // better than a partial round of big ones.  Measured (us, B out of cache, big tiles / best smaller tile): 8192 x 768, K = 3072 (96 big tiles) 59 / 37, 4096 x 2048,
-  // K = 2048 (128) 42 / 31; from 5/8 of a round on the big tiles mostly win: 8192 x 2304, K = 768 (288) 38.0 / 39.6, 8192 x 3072 (384) 43.2 / 47.4, 8192 x 1536, K = 1536 (192) 35.7 / 36.4.
+  // K = 2048 (128) 42 / 31, 8192 x 1024, K = 768 (128) 21.2 / 15.5.  Right above 128 both take the same within 6 % (the smaller ones need a second round as well): 8700 x 1024, K = 2048 (136) 42.0 / 40.5, 4096 x 2304,
+  // K = 768 (144) 20.9 / 22.0, 8192 x 1280, K = 2048 (160) 43.3 / 41.3, 8192 x 1152, K = 768 (160) 21.0 / 21.7; further up the big ones win: 6144 x 2048, K = 8192 (192) 159 / 179, 8192 x 1792, K = 1792 (224)
+  // 42.9 / 56.4, 8192 x 2048, K = 2048 (256) 53.7 / 59.8.
   const long tiles256 = (long)((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   if (tiles256 <= 128 && g_gemm_small_tiles.load(std::memory_order_relaxed) && g_gemm_variant.load(std::memory_order_relaxed) == 1 &&
       k_gemm_nt_ring(st, A, lda, B, ldb, C, ldc, M, N, K, epi, R) == 0)
