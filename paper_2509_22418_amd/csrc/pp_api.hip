@@ -586,10 +586,10 @@ static void gemm_dw_tn(pp_model* m, const void* A, int lda, int m_blk, long a_bl
   const size_t es = esize(m->cfg);
   // Up to 256 tiles of 128 x 128 -- the row-block slices, which need split-K anyway, and d x d -- the transpose-read kernel beats transposing
   // both operands and running the 256 x 256-tile NT kernel; far above that the NT kernel's higher rate outweighs the two extra passes.  The line
-  // is from a kernel that waited for all its loads at every transpose read; the present one (us, token-major / copies + NT): 2048 x 2048 over 16384
-  // rows (256 tiles) 206 / 301, 3072 x 2048 over 8192 (384) 125 / 164, 4096 x 2048 over 16384 (512) 286 / 341, 6144 x 2048 (768) 472 / 404, 32000 x 2048
-  // over 8192 (4000) 1154 / 1008, 32000 x 768 over 8192 (1500) 441 / 574.  Same bits either way.  A token count that is not a multiple of 64 always
-  // comes here: the transposed copies would have rows the NT kernel does not take.
+  // is from a kernel that waited for all its loads at every transpose read; with the present one the token-major form is faster up to 512 tiles and at d = 768 (us, token-major / copies + NT: 2048 x
+  // 2048 over 16384 rows (256 tiles) 206 / 301, 3072 x 2048 over 8192 (384) 125 / 164, 4096 x 2048 over 16384 (512) 286 / 341, 32000 x 768 over 8192 (1500) 441 / 574; against 6144 x 2048 (768) 472 /
+  // 404, 32000 x 2048 over 8192 (4000) 1154 / 1008).  It has not been moved: below 1024 tiles the two forms sum over other K ranges, so gradients would have other bits.  A token count
+  // that is not a multiple of 64 always comes here: the transposed copies would have rows the NT kernel does not take.
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
   // The ranges, and with them the order of a gradient's sums, are doubled until the chip has 512 workgroups (two per unit).  Numbers that fill one round better are faster (768 x 768
   // over 8192 rows, 36 tiles: 26.6 us in 16 ranges, 18.7 in 12; with the sum of the ranges 34.3 / 24.9) but add in another order; the same ranges two to a
