@@ -14,6 +14,7 @@ OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 def test_no_kernel_addresses_its_registers_by_index(tmp_path):
     """A loop over accumulators that is not unrolled in full becomes s_set_gpr_idx around every access (the fp32-multiply attention backward at head dim 128: 8448 of
     them, 1.1 to 1.2 times the time)."""
+    pp.load_library()          # builds it if it has never been built
     lib = shutil.copy(pp.lib_path(), tmp_path / "lib.so")
     subprocess.run([OBJDUMP, "--offloading", str(lib)], check=True, capture_output=True, cwd=tmp_path)
     text = "".join(subprocess.run([OBJDUMP, "-d", str(o)], check=True, capture_output=True, text=True).stdout for o in sorted(tmp_path.glob("*gfx950*")))

@@ -46,7 +46,7 @@ def tensors(B, S, h, dh, dtype):
 
 def runs_on_mfma(dt, qkv, do, B, S, h, dh):
     """(forward, backward): whether the C++ entries take the shape (they launch nothing where they do not)."""
-    lib, P, I = ctypes.CDLL(pp.lib_path()), ctypes.c_void_p, ctypes.c_int
+    lib, P, I = pp.load_library(), ctypes.c_void_p, ctypes.c_int
     fwd = lib["_ZN2pp14k_attn_fwd_f32EP12ihipStream_tiPKvPvPfiiii"]
     bwd = lib["_ZN2pp14k_attn_bwd_f32EP12ihipStream_tiPKvS3_PKfS3_PvPfiiii"]
     fwd.argtypes, bwd.argtypes = [P, I, P, P, P, I, I, I, I], [P, I, P, P, P, P, P, P, I, I, I, I]

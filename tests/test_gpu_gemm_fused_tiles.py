@@ -25,7 +25,7 @@ def test_same_bits_as_big_tiles(d, h, ff, B, S, mname):
     if S == 1:
         tgt[:] = 7
     weights, out = gen.make_weights(cfg, seed=5), []
-    on_small = ctypes.CDLL(pp.lib_path())["_ZN2pp18gemm_fused_on_ringEiiii"]
+    on_small = pp.load_library()["_ZN2pp18gemm_fused_on_ringEiiii"]
     on_small.restype = ctypes.c_bool
     pp.pp_set_option(None, "gemm_small_tiles", 1)
     n = ff if mname == "all" else mask["ffn_hi"] - mask["ffn_lo"]

@@ -1,7 +1,5 @@
 """The smaller-tile NT GEMM around the length of its ring: every tile with 1 .. 9 K steps (fewer than, as many as and more than the stages, odd and
 even counts) and on both sides of a tile's edge, against fp64 on the same bf16 inputs."""
-import ctypes
-
 import pytest
 import torch
 
@@ -28,7 +26,7 @@ LONG = [(1003, 520, 2048, False, 1), (500, 1000, 2112, True, 1), (2100, 512, 204
 
 
 def tile(M, N, K):
-    return ctypes.CDLL(pp.lib_path())["_ZN2pp14gemm_ring_tileEiii"](M, N, K)
+    return pp.load_library()["_ZN2pp14gemm_ring_tileEiii"](M, N, K)
 
 
 def test_every_tile_and_length_is_among_the_cases():

@@ -29,7 +29,7 @@ FUSED = [(SWIGLU, 3055, 3072, 768, True),           # 43.9 / 36.4
 
 @pytest.mark.parametrize("epi,M,n,K,small", FUSED)
 def test_fused_gemms_run_on_the_faster_tiles(epi, M, n, K, small):
-    f = ctypes.CDLL(pp.lib_path())["_ZN2pp18gemm_fused_on_ringEiiii"]
+    f = pp.load_library()["_ZN2pp18gemm_fused_on_ringEiiii"]
     f.restype = ctypes.c_bool
     pp.pp_set_option(None, "gemm_small_tiles", 1)
     assert f(epi, M, n, K) == small
@@ -53,6 +53,6 @@ F32 = [(1024, 512, 2048, True, True),           # 32.1 / 26.3
 
 @pytest.mark.parametrize("M,N,K,vec,ahead", F32)
 def test_fp32_gemm_runs_the_faster_loop(M, N, K, vec, ahead):
-    f = ctypes.CDLL(pp.lib_path())["_ZN2pp20gemm_f32_reads_aheadElib"]
+    f = pp.load_library()["_ZN2pp20gemm_f32_reads_aheadElib"]
     f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_long, ctypes.c_int, ctypes.c_bool]
     assert f(-(-M // 32) * -(-N // 32), K, vec) == ahead
